@@ -1530,8 +1530,18 @@ static cmg_status ensure_rhs_plan(cmg_problem* P) {
   auto& own = P->owned;
   int32_t *uncut, *cut, *act;
   int64_t* off;
-  double *cx, *cw, *ct0, *ct1, *loc;
+  double *cx, *cw, *ct0, *ct1, *loc, *part;
   uint8_t* ce;
+  // chunks of at most kRhsChunk columns of one cut cell
+  std::vector<int32_t> choff(R.cut.size() + 1, 0), chcell;
+  for (size_t i = 0; i < R.cut.size(); ++i) {
+    const int64_t nc = (R.col_off[i + 1] - R.col_off[i] + cmg::kRhsChunk - 1) / cmg::kRhsChunk;
+    chcell.insert(chcell.end(), static_cast<size_t>(nc), static_cast<int32_t>(i));
+    choff[i + 1] = static_cast<int32_t>(chcell.size());
+  }
+  int32_t *dchoff, *dchcell;
+  TRY(upload(own, choff, &dchoff));
+  TRY(upload(own, chcell, &dchcell));
   TRY(upload(own, R.uncut, &uncut));
   TRY(upload(own, R.cut, &cut));
   TRY(upload(own, R.col_off, &off));
@@ -1543,7 +1553,12 @@ static cmg_status ensure_rhs_plan(cmg_problem* P) {
   TRY(upload(own, R.act_id, &act));
   const int nl = static_cast<int>(std::pow(cfg.k + 1, cfg.dim));
   TRY(alloc_zero(own, static_cast<size_t>(R.n_active) * nl, &loc));
+  TRY(alloc_zero(own, chcell.size() * nl, &part));
   TRY(settle());
+  D.n_chunk = static_cast<int64_t>(chcell.size());
+  D.chunk_off = dchoff;
+  D.chunk_cell = dchcell;
+  D.part = part;
   D.uncut = uncut;
   D.cut = cut;
   D.col_off = off;
@@ -1560,7 +1575,8 @@ static cmg_status ensure_rhs_plan(cmg_problem* P) {
   D.nq = cfg.quad_n;
   cmg::gauss_legendre(cfg.quad_n, D.tx, D.tw);
   P->rhs_bytes = R.uncut.size() * 4 + R.cut.size() * 4 + R.col_off.size() * 8 + R.cx.size() * 8 +
-                 R.cw.size() * 24 + R.ce.size() + R.act_id.size() * 4 + static_cast<size_t>(R.n_active) * nl * 8;
+                 R.cw.size() * 24 + R.ce.size() + R.act_id.size() * 4 + static_cast<size_t>(R.n_active) * nl * 8 +
+                 (choff.size() + chcell.size()) * 4 + chcell.size() * nl * 8;
   P->rhs_ready = true;
   return CMG_OK;
 }
@@ -1578,7 +1594,12 @@ cmg_status cmg_rhs_fourier_device(cmg_problem* p, int n_modes, const int* kappa,
   for (int q = 0; q < n_modes; ++q) {
     for (int j = 0; j < d; ++j) M.kappa[q][j] = kappa[q * d + j];
     M.amp[q] = amp[q];
-    M.phase[q] = phase[q];
+    M.phase[q] = phase[q] / M_PI;
+  }
+  for (int j = 0; j < d; ++j) {
+    for (int q = 0; q < n_modes; ++q) M.ord[j][q] = static_cast<uint8_t>(q);
+    std::stable_sort(M.ord[j], M.ord[j] + n_modes,
+                     [&](uint8_t a, uint8_t b) { return M.kappa[a][j] < M.kappa[b][j]; });
   }
   const cmg::HostLevel& L = p->H.levels.back();
   DevLevel& D = p->lv.back();

@@ -211,10 +211,13 @@ std::recursive_mutex& device_mutex();
 // host set-up (cell vectors of every active cell, then one gather per DoF;
 // every sum in a fixed order, so the result is the same in every run).
 constexpr int kMaxModes = 32;
+constexpr int kRhsChunk = 256;  // quadrature columns of one block of the cut-cell kernel
+constexpr int kRhsPow = 8;      // complex products before a power is formed anew
 struct RhsModes {
   int n;
   int kappa[kMaxModes][3];
-  double amp[kMaxModes], phase[kMaxModes];
+  double amp[kMaxModes], phase[kMaxModes];  // phase / pi
+  uint8_t ord[3][kMaxModes];                // the modes in increasing order of kappa[.][e], per direction e
 };
 struct RhsPlanDev {
   int N, nn;                 // cells / lattice nodes per direction
@@ -223,6 +226,10 @@ struct RhsPlanDev {
   const int32_t* uncut;      // background cells of the active uncut cells
   const int32_t* cut;        // background cells of the cut cells
   const int64_t* col_off;    // volume columns of cut cell i: col_off[i] .. col_off[i+1]
+  int64_t n_chunk;           // runs of at most kRhsChunk columns of one cut cell
+  const int32_t* chunk_off;  // chunks of cut cell i: chunk_off[i] .. chunk_off[i+1]
+  const int32_t* chunk_cell; // cut cell of every chunk
+  double* part;              // partial cell vectors, (k+1)^d per chunk
   const double* cx;          // base points, SoA (dim arrays of n_col)
   const double* cw;
   const double* ct0;
@@ -232,7 +239,7 @@ struct RhsPlanDev {
   double* loc;               // cell vectors, (k+1)^d per active cell
   double coef[4][4];         // monomial coefficients of the 1-D GLL basis, psi_a(t) = sum_m coef[a][m] t^m
   double gx[8], gw[8];       // k+3 Gauss points / weights on [0, 1] (uncut cells)
-  double tx[16], tw[16];     // quad_n points / weights on [0, 1] (along a column)
+  double tx[16], tw[16];     // quad_n points / weights on [0, 1] (along a column), zero beyond
   int nq;
 };
 hipError_t launch_rhs_fourier(int d, int k, const RhsPlanDev& R, const RhsModes& M, const int32_t* dof_node,

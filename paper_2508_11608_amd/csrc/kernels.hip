@@ -743,7 +743,7 @@ template <int D, int K, typename T>
 __device__ __forceinline__ void interior_step_body(KLevel L, const int32_t* __restrict__ verts, int nv,
                                                    T* __restrict__ x, const T* __restrict__ b) {
   using S = Shape<D, K>;
-  constexpr int NP = S::NP, NP1 = S::NP1, NC = S::NC, NC1 = S::NC1, PPB = S::PPB, N1 = S::N1, NL = S::NL;
+  constexpr int NP = S::NP, NP1 = S::NP1, NC = S::NC, NC1 = S::NC1, PPB = S::PPB, N1 = S::N1;
   // the level tables this kernel reads, in the precision of the path: 1-D mass,
   // scaled 1-D stiffness, fast-diagonalisation eigenvectors and inverse sums
   __shared__ T cm1[N1 * N1], ck1[N1 * N1], cfs[NP1 * NP1], cfd[NP];
@@ -2741,16 +2741,6 @@ hipError_t launch_copy(int64_t n, const double* x, double* y, hipStream_t s) {
 namespace cmg {
 namespace dev {
 
-__device__ __forceinline__ double rhs_f(const RhsModes& M, int D, const double* x) {
-  double v = 0.0;
-  for (int q = 0; q < M.n; ++q) {
-    double arg = M.phase[q];
-    for (int j = 0; j < D; ++j) arg += M_PI * M.kappa[q][j] * x[j];
-    v += M.amp[q] * cos(arg);
-  }
-  return v;
-}
-
 template <int K>
 __device__ __forceinline__ void rhs_basis(const RhsPlanDev& R, double t, double* psi) {
 #pragma unroll
@@ -2763,10 +2753,50 @@ __device__ __forceinline__ void rhs_basis(const RhsPlanDev& R, double t, double*
 }
 
 // Cell vectors of the uncut active cells: tensor Gauss rule with k+3 points
-// per direction, one thread per cell.
+// per direction.  On a cell with corner lo every mode is a product,
+//   cos(pi kappa . x + phase) = Re e^{i(phase + pi kappa . lo)} prod_j e^{i pi kappa_j h t_j},
+// so the rule factorises: its sum against psi_a is one phase per cell and mode
+// times a complex tensor T_q[a] = prod_j sum_g h w_g psi_{a_j}(g) e^{i pi kappa_j h g} that
+// no cell enters.  Every block forms T_q in LDS; a thread then takes one cell,
+// one sincospi per mode and 2 (k+1)^d multiply-adds instead of (k+3)^d cosines.
+// Union of two balls, Q2, 64^3 cells, 16 modes, 15,382 uncut cells: 504 -> 25 us.
 template <int D, int K>
 __global__ __launch_bounds__(256) void k_rhs_uncut(RhsPlanDev R, RhsModes M) {
   constexpr int N1 = K + 1, NL = Pow<N1, D>::v, NG = K + 3;
+  __shared__ double G[kMaxModes][D][N1][2];
+  __shared__ double T[kMaxModes][NL][2];
+  for (int t = threadIdx.x; t < M.n * D * N1; t += blockDim.x) {
+    const int a = t % N1, j = (t / N1) % D, q = t / (N1 * D);
+    double re = 0.0, im = 0.0;
+    for (int g = 0; g < NG; ++g) {
+      double psi[N1], s, c, pa = 0.0;
+      rhs_basis<K>(R, R.gx[g], psi);
+#pragma unroll
+      for (int m = 0; m < N1; ++m) pa = m == a ? psi[m] : pa;
+      sincospi(M.kappa[q][j] * (R.h * R.gx[g]), &s, &c);
+      pa *= R.h * R.gw[g];
+      re += pa * c;
+      im += pa * s;
+    }
+    G[q][j][a][0] = re;
+    G[q][j][a][1] = im;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < M.n * NL; t += blockDim.x) {
+    const int q = t / NL;
+    int ra = t % NL;
+    double re = M.amp[q], im = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      const double gr = G[q][j][ra % N1][0], gi = G[q][j][ra % N1][1], r0 = re;
+      ra /= N1;
+      re = r0 * gr - im * gi;
+      im = r0 * gi + im * gr;
+    }
+    T[q][t % NL][0] = re;
+    T[q][t % NL][1] = im;
+  }
+  __syncthreads();
   const int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (u >= R.n_uncut) return;
   const int c = R.uncut[u];
@@ -2779,115 +2809,188 @@ __global__ __launch_bounds__(256) void k_rhs_uncut(RhsPlanDev R, RhsModes M) {
       r /= R.N;
     }
   }
-  double hd = 1.0;
-#pragma unroll
-  for (int j = 0; j < D; ++j) hd *= R.h;
   double acc[NL];
 #pragma unroll
   for (int a = 0; a < NL; ++a) acc[a] = 0.0;
-  constexpr int NPT = Pow<NG, D>::v;
-  for (int p = 0; p < NPT; ++p) {
-    double x[3], psi[3][N1], w = hd;
-    int r = p;  // the same for every thread: the table loads are scalar
+  for (int q = 0; q < M.n; ++q) {
+    double th = M.phase[q], sn, cs;
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int m = r % NG;
-      r /= NG;
-      x[j] = lo[j] + R.h * R.gx[m];
-      w *= R.gw[m];
-      rhs_basis<K>(R, R.gx[m], psi[j]);
-    }
-    const double fv = rhs_f(M, D, x) * w;
+    for (int j = 0; j < D; ++j) th += M.kappa[q][j] * lo[j];
+    sincospi(th, &sn, &cs);
 #pragma unroll
-    for (int a = 0; a < NL; ++a) {
-      double v = fv;
-      int ra = a;
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        v *= psi[j][ra % N1];
-        ra /= N1;
-      }
-      acc[a] += v;
-    }
+    for (int a = 0; a < NL; ++a) acc[a] += cs * T[q][a][0] - sn * T[q][a][1];
   }
   double* out = R.loc + (int64_t)R.act_id[c] * NL;
 #pragma unroll
   for (int a = 0; a < NL; ++a) out[a] = acc[a];
 }
 
-// Cell vectors of the cut cells: one block per cut cell, thread t takes the
-// columns t, t + 256, ... of the cell; along a column only direction e varies,
-// so each column sums f w psi_{a_e} per a_e and spreads it with the basis
-// factors of the other directions.  The block's partial vectors are reduced
-// in a fixed order (butterfly within each wavefront, then the four
-// wavefronts in order).
-template <int D, int K>
+// Partial cell vectors of the cut cells: one block per chunk of at most
+// kRhsChunk quadrature columns of one cell, one column per thread.  A kinked
+// cell of a union has up to hundreds of times the columns of a smooth one, so
+// a block per cell (the former split) ran as long as its longest cell's serial
+// loop: 22,459 -> 858 us on the union of two balls, Q2, 64^3 cells, 16 modes (6.6
+// million columns, 26,167 chunks; now bound by FP64 arithmetic, about 2,000
+// operations a column).
+// Along a column only direction e varies, so f there is sum_m C_m cos(pi m t)
+// - S_m sin(pi m t) over the distinct m = kappa_e, with (C_m, S_m) summed over
+// the modes of that m at the column's base point.  The modes come sorted by
+// kappa_e (M.ord), and e^{i pi m t} moves from one m to the next by complex
+// multiplication with e^{i pi t} (started again from sincospi after kRhsPow
+// products, so at most that many roundings add up).  Each column leaves its
+// 1-D factors in LDS (psi_a of the base point, along e the weighted sum of f
+// psi_a), and the block then sums their products over the columns for every
+// cell node, in a fixed order.
+template <int D, int K, int NQ>
 __global__ __launch_bounds__(256) void k_rhs_cut(RhsPlanDev R, RhsModes M) {
-  constexpr int N1 = K + 1, NL = Pow<N1, D>::v;
-  const int i = blockIdx.x;
-  const int c = R.cut[i];
-  double lo[3];
-  {
-    int r = c;
+  constexpr int N1 = K + 1, NL = Pow<N1, D>::v, NG = kRhsChunk / NL;
+  static_assert(NG >= 1, "a thread per cell node at least");
+  __shared__ double F[D][N1][kRhsChunk + 1];
+  __shared__ double gs[NG][NL];
+  __shared__ double mk[D][kMaxModes][D], ma[D][kMaxModes], mp[D][kMaxModes];
+  __shared__ int me[D][kMaxModes];
+  for (int t = threadIdx.x; t < D * M.n; t += blockDim.x) {
+    const int e = t / M.n, i = t % M.n, q = M.ord[e][i];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      lo[j] = R.lo + (r % R.N) * R.h;
-      r /= R.N;
-    }
+    for (int j = 0; j < D; ++j) mk[e][i][j] = j == e ? 0.0 : (double)M.kappa[q][j];
+    ma[e][i] = M.amp[q];
+    mp[e][i] = M.phase[q];
+    me[e][i] = M.kappa[q][e];
   }
-  double acc[NL];
+  const int ch = blockIdx.x;
+  const int ci = R.chunk_cell[ch];
+  const int64_t c0 = R.col_off[ci] + (int64_t)kRhsChunk * (ch - R.chunk_off[ci]);
+  const int64_t left = R.col_off[ci + 1] - c0;
+  const int n = left < kRhsChunk ? (int)left : kRhsChunk;
+  __syncthreads();
+  const int tid = threadIdx.x;
+  if (tid < n) {
+    const int64_t col = c0 + tid;
+    double lo[D], x[D];
+    {
+      int r = R.cut[ci];
 #pragma unroll
-  for (int a = 0; a < NL; ++a) acc[a] = 0.0;
-  const int64_t c0 = R.col_off[i], c1 = R.col_off[i + 1];
-  for (int64_t col = c0 + threadIdx.x; col < c1; col += blockDim.x) {
-    const int e = R.ce[col];
-    double x[3], psi[3][N1];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      x[j] = R.cx[j * R.n_col + col];
-      rhs_basis<K>(R, (x[j] - lo[j]) / R.h, psi[j]);
+      for (int j = 0; j < D; ++j) {
+        lo[j] = R.lo + (r % R.N) * R.h;
+        r /= R.N;
+      }
     }
-    const double w = R.cw[col], t0 = R.ct0[col], t1 = R.ct1[col];
+    const int e = R.ce[col];
+#pragma unroll
+    for (int j = 0; j < D; ++j) x[j] = R.cx[j * R.n_col + col];
+    const double w = R.cw[col], t0 = R.ct0[col], len = R.ct1[col] - t0;
+    double f[NQ], zr[NQ], zi[NQ], pr[NQ], pi[NQ];
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      f[t] = 0.0;
+      sincospi(t0 + len * R.tx[t], &zi[t], &zr[t]);
+      pr[t] = 1.0;
+      pi[t] = 0.0;
+    }
+    int cur = 0, used = 0;  // e^{i pi cur t} is held; products since it was last formed
+    for (int i = 0; i < M.n;) {
+      const int m = me[e][i];
+      double C = 0.0, S = 0.0;
+      do {
+        double th = mp[e][i], sn, cs;
+#pragma unroll
+        for (int j = 0; j < D; ++j) th += j == e ? 0.0 : mk[e][i][j] * x[j];
+        sincospi(th, &sn, &cs);
+        C += ma[e][i] * cs;
+        S += ma[e][i] * sn;
+        ++i;
+      } while (i < M.n && me[e][i] == m);
+      if (m < cur || (unsigned)m - (unsigned)cur > (unsigned)(kRhsPow - used)) {
+#pragma unroll
+        for (int t = 0; t < NQ; ++t) sincospi(m * (t0 + len * R.tx[t]), &pi[t], &pr[t]);
+        used = 0;
+      } else {
+        for (int s = cur; s < m; ++s) {
+#pragma unroll
+          for (int t = 0; t < NQ; ++t) {
+            const double r0 = pr[t];
+            pr[t] = r0 * zr[t] - pi[t] * zi[t];
+            pi[t] = r0 * zi[t] + pi[t] * zr[t];
+          }
+        }
+        used += m - cur;
+      }
+      cur = m;
+#pragma unroll
+      for (int t = 0; t < NQ; ++t) f[t] += C * pr[t] - S * pi[t];
+    }
+    double loe = lo[0];
+#pragma unroll
+    for (int j = 1; j < D; ++j) loe = j == e ? lo[j] : loe;
     double ae[N1];
 #pragma unroll
     for (int a = 0; a < N1; ++a) ae[a] = 0.0;
-    for (int t = 0; t < R.nq; ++t) {
-      double xt[3];
 #pragma unroll
-      for (int j = 0; j < D; ++j) xt[j] = j == e ? t0 + (t1 - t0) * R.tx[t] : x[j];
-      const double fv = rhs_f(M, D, xt) * w * (t1 - t0) * R.tw[t];
+    for (int t = 0; t < NQ; ++t) {
       double pe[N1];
-      rhs_basis<K>(R, (xt[e] - lo[e]) / R.h, pe);
+      rhs_basis<K>(R, (t0 + len * R.tx[t] - loe) / R.h, pe);
+      const double fv = f[t] * w * len * R.tw[t];
 #pragma unroll
       for (int a = 0; a < N1; ++a) ae[a] += fv * pe[a];
     }
 #pragma unroll
-    for (int a = 0; a < NL; ++a) {
-      double v = 1.0, s = 0.0;
-      int ra = a;
+    for (int j = 0; j < D; ++j) {
+      double psi[N1];
+      rhs_basis<K>(R, (x[j] - lo[j]) / R.h, psi);
 #pragma unroll
-      for (int j = 0; j < D; ++j) {
-        const int aj = ra % N1;
-        ra /= N1;
-        if (j == e) s = ae[aj];
-        else v *= psi[j][aj];
-      }
-      acc[a] += v * s;
+      for (int a = 0; a < N1; ++a) F[j][a][tid] = j == e ? ae[a] : psi[a];
     }
   }
-  __shared__ double wsum[4][NL];
-  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  __syncthreads();
+  const int g = tid / NL, a = tid % NL;
+  constexpr int RUN = (kRhsChunk + NG - 1) / NG;  // columns of one group of NL threads
+  if (g < NG) {
+    const double* fa[D];
+    int ra = a;
 #pragma unroll
-  for (int a = 0; a < NL; ++a) {
-    double v = acc[a];
+    for (int j = 0; j < D; ++j) {
+      fa[j] = F[j][ra % N1];
+      ra /= N1;
+    }
+    double s = 0.0;
+    const int hi = (g + 1) * RUN < n ? (g + 1) * RUN : n;
+    for (int q = g * RUN; q < hi; ++q) {
+      double v = fa[0][q];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) wsum[wave][a] = v;
+      for (int j = 1; j < D; ++j) v *= fa[j][q];
+      s += v;
+    }
+    gs[g][a] = s;
+  }
+  __syncthreads();
+  if (tid < NL) {
+    double s = gs[0][tid];
+#pragma unroll 1
+    for (int q = 1; q < NG; ++q) s += gs[q][tid];
+    R.part[(int64_t)ch * NL + tid] = s;
+  }
+}
+
+// Cell vectors of the cut cells: the partial vectors of a cell's chunks summed
+// in a fixed order (groups of NL threads take every NG-th chunk, then the
+// groups in order); zero for a cell without columns.
+template <int D, int K>
+__global__ __launch_bounds__(256) void k_rhs_cut_sum(RhsPlanDev R) {
+  constexpr int NL = Pow<K + 1, D>::v, NG = 256 / NL;
+  __shared__ double gs[NG][NL];
+  const int ci = blockIdx.x, g = threadIdx.x / NL, a = threadIdx.x % NL;
+  const int lo = R.chunk_off[ci], hi = R.chunk_off[ci + 1];
+  if (g < NG) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int q = lo + g; q < hi; q += NG) s += R.part[(int64_t)q * NL + a];
+    gs[g][a] = s;
   }
   __syncthreads();
   if (threadIdx.x < NL) {
-    const int a = threadIdx.x;
-    R.loc[(int64_t)R.act_id[c] * NL + a] = (wsum[0][a] + wsum[1][a]) + (wsum[2][a] + wsum[3][a]);
+    double s = gs[0][a];
+    for (int q = 1; q < NG && q < hi - lo; ++q) s += gs[q][a];
+    R.loc[(int64_t)R.act_id[R.cut[ci]] * NL + a] = s;
   }
 }
 
@@ -2946,9 +3049,17 @@ hipError_t launch_rhs_fourier(int d, int k, const RhsPlanDev& R, const RhsModes&
     if (R.n_uncut > 0)
       hipLaunchKernelGGL((dev::k_rhs_uncut<D.value, K.value>), dim3(static_cast<unsigned>((R.n_uncut + 255) / 256)),
                          dim3(256), 0, s, R, M);
+    if (R.n_chunk > 0) {
+      const dim3 g(static_cast<unsigned>(R.n_chunk)), t(kRhsChunk);
+      // quad_n points in registers; the default rule has 14, any other is padded to 16 with zero weights
+      if (R.nq == 14)
+        hipLaunchKernelGGL((dev::k_rhs_cut<D.value, K.value, 14>), g, t, 0, s, R, M);
+      else
+        hipLaunchKernelGGL((dev::k_rhs_cut<D.value, K.value, 16>), g, t, 0, s, R, M);
+    }
     if (R.n_cut > 0)
-      hipLaunchKernelGGL((dev::k_rhs_cut<D.value, K.value>), dim3(static_cast<unsigned>(R.n_cut)), dim3(256), 0, s,
-                         R, M);
+      hipLaunchKernelGGL((dev::k_rhs_cut_sum<D.value, K.value>), dim3(static_cast<unsigned>(R.n_cut)), dim3(256), 0,
+                         s, R);
     if (n_dofs > 0)
       hipLaunchKernelGGL((dev::k_rhs_gather<D.value, K.value>), dim3(static_cast<unsigned>((n_dofs + 255) / 256)),
                          dim3(256), 0, s, R, dof_node, n_dofs, b);
