@@ -694,19 +694,11 @@ cmg_status colour_step(cmg_problem* P, int l, bool interior, int colour, hipStre
   if (G.n_patch == 0) return CMG_OK;
   {
     KTimer t(P, kCutSolve, l, s);
-    if constexpr (std::is_same<T, float>::value) {
-      if (multi && G.inv_tiles) {
-        HIP_TRY(cmg::launch_cut_solve_mfma(d, k, kl<T>(D), G, v.x, v.b, v.W, v.dbuf, ncol, s));
-      } else {
-        HIP_TRY(cmg::launch_cut_solve<T>(d, k, kl<T>(D), G, v.x, v.b, v.dbuf, s, ncol, nullptr, cmg::CopyJob(),
-                                         P->launch));
-      }
-    } else if (multi) {
-      HIP_TRY(cmg::launch_cut_solve_cols(d, k, kl<T>(D), G, v.x, v.b, v.W, v.dbuf, ncol, s));
-    } else {
+    if (multi)
+      HIP_TRY(cmg::launch_cut_cols<T>(d, k, kl<T>(D), G, v.x, v.b, v.dbuf, ncol, s, nullptr, cmg::CopyJob(), P->launch));
+    else
       HIP_TRY(cmg::launch_cut_solve<T>(d, k, kl<T>(D), G, v.x, v.b, v.dbuf, s, ncol, nullptr, cmg::CopyJob(),
                                        P->launch));
-    }
   }
   KTimer t(P, kCutUpdate, l, s);
   HIP_TRY(cmg::launch_cut_update<T>(G, v.dbuf, v.x, D.kl64.n_nodes, s, ncol));
@@ -716,13 +708,11 @@ cmg_status colour_step(cmg_problem* P, int l, bool interior, int colour, hipStre
 // The cut colour steps of one smoothing pass (n_c sweeps over the colours
 // that have cut patches; reversed in the post-smoother).  Every step reads x
 // as it was at the start of the step (same-coloured patches are updated
-// together).  With the single-matrix-row kernel the steps alternate between two
-// x buffers: step i reads X[i % 2] and writes X[(i + 1) % 2], where the patch
+// together).  The steps alternate between two x buffers: step i reads X[i % 2] and writes X[(i + 1) % 2], where the patch
 // blocks store x + d on the colour's internal DoFs and copy blocks bring over
 // the previous colour's DoFs that the current colour does not own; X1 is made
 // equal to X0 on the cut region first, and an even number of steps ends in
-// X0 (an odd last step uses the correction buffer).  The matrix-core kernel
-// keeps the correction buffer and a separate update for every step.
+// X0 (an odd last step uses the correction buffer).
 template <typename T>
 cmg_status cut_steps(cmg_problem* P, int l, bool post, hipStream_t s, int ncol, bool multi) {
   const int d = P->H.cfg.dim, k = P->H.cfg.k;
@@ -734,15 +724,8 @@ cmg_status cut_steps(cmg_problem* P, int l, bool post, hipStream_t s, int ncol, 
     for (int c = 0; c < C; ++c)
       if (cutg<T>(D, c).n_patch > 0) seq.push_back(c);
   if (post) std::reverse(seq.begin(), seq.end());
-  // the multi-column kernels (FP32 matrix cores, FP64 all columns per block)
-  // write corrections and take the separate update
-  bool cols = multi;
-  if constexpr (std::is_same<T, float>::value) {
-    cols = false;
-    for (int c = 0; c < C; ++c) cols = cols || (multi && cutg<T>(D, c).inv_tiles);
-  }
   size_t npp = seq.size() - seq.size() % 2;
-  if (cols || !v.x1 || npp == 0) npp = 0;
+  if (!v.x1) npp = 0;
   if (npp > 0) {
     KTimer t(P, kCutUpdate, l, s);
     HIP_TRY(cmg::launch_copy_nodes<T>(D.region, D.n_region, v.x, v.x1, D.kl64.n_nodes, s, ncol));
@@ -753,8 +736,12 @@ cmg_status cut_steps(cmg_problem* P, int l, bool post, hipStream_t s, int ncol, 
     cmg::CopyJob cj;
     if (i > 0) cj = cmg::cut_copy_job(d, k, cutg<T>(D, seq[i - 1]), post ? 2 : 1);
     KTimer t(P, kCutSolve, l, s);
-    HIP_TRY(cmg::launch_cut_solve<T>(d, k, kl<T>(D), G, X[i % 2], v.b, v.dbuf, s, ncol, X[(i + 1) % 2], cj,
-                                     P->launch));
+    if (multi)
+      HIP_TRY(cmg::launch_cut_cols<T>(d, k, kl<T>(D), G, X[i % 2], v.b, v.dbuf, ncol, s, X[(i + 1) % 2], cj,
+                                      P->launch));
+    else
+      HIP_TRY(cmg::launch_cut_solve<T>(d, k, kl<T>(D), G, X[i % 2], v.b, v.dbuf, s, ncol, X[(i + 1) % 2], cj,
+                                       P->launch));
   }
   for (size_t i = npp; i < seq.size(); ++i) TRY(colour_step<T>(P, l, false, seq[i], s, ncol, multi));
   return CMG_OK;

@@ -63,7 +63,7 @@ struct CutGroupDev {
   const int32_t* cell_cut;   // per patch and cell o of its 2^d: cut-cell index, -1 if uncut or outside
   const uint16_t* cell_fg;   // per patch and cell o: flags | ghost bits << 8 (0 outside the box)
   const void* inv;           // symmetric dense inverses, scalar type of the path
-  const float* inv_tiles;    // FP32 inverses in MFMA tile order (see k_cut_solve_mfma), or null
+  const float* inv_tiles;    // FP32 inverses in MFMA tile order (see k_cut_cols), or null
   const int64_t* tile_off;   // tile offsets, n_patch + 1, or null
   const uint8_t* nxt;        // per node: bit 0 (1) also internal to the next (previous) cut colour
   template <typename T>
@@ -154,14 +154,13 @@ CopyJob cut_copy_job(int d, int k, const CutGroupDev& Gp, int mask);
 template <typename T>
 hipError_t launch_copy_nodes(const int32_t* nodes, int64_t n, const T* src, T* dst, int64_t ld, hipStream_t s,
                              int ncol = 1);
-// FP32, ncol <= kMaxCols columns, local solves on the matrix cores (needs
-// inv_tiles); W is the ghost-face work buffer (ncol columns), rewritten here.
-// FP64 counterpart for several columns: every inverse and cell row read once
-// for all columns (plain FMA); corrections into dbuf like the FP32 kernel.
-hipError_t launch_cut_solve_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const double* x,
-                                 const double* b, double* W, double* dbuf, int ncol, hipStream_t s);
-hipError_t launch_cut_solve_mfma(int d, int k, const KLevel& L, const CutGroupDev& G, const float* x, const float* b,
-                                 float* W, float* dbuf, int ncol, hipStream_t s);
+// The cut colour step of 1 <= ncol <= kMaxCols columns, one patch block for all
+// of them, on the matrix cores (FP32 needs inv_tiles); xb and cj as in
+// launch_cut_solve.
+template <typename T>
+hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const T* x, const T* b, T* dbuf,
+                           int ncol, hipStream_t s, T* xb = nullptr, const CopyJob& cj = CopyJob(),
+                           const LaunchPolicy& lp = LaunchPolicy());
 template <typename T>
 hipError_t launch_cut_update(const CutGroupDev& G, const T* dbuf, T* x, int64_t ldx, hipStream_t s, int ncol = 1);
 template <typename T>

@@ -28,13 +28,14 @@
 //     a same-coloured neighbour) and dense inverse GEMV; every patch of the
 //     colour must see the state at the start of the step, so the steps of a
 //     smoothing pass alternate between two x buffers (read one, write x + d
-//     and the previous colour's DoFs into the other), or, for the matrix-core
-//     kernel, write the corrections to a buffer that a second kernel adds.
+//     and the previous colour's DoFs into the other); an odd last step writes
+//     the corrections to a buffer that a second kernel adds.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -1564,397 +1565,573 @@ __global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G,
     dbuf[off + tid] = dv;
 }
 
-// Residual rows of one cut patch for NCOL columns at once.  The patch closure
-// of every column is staged node-major in LDS (the columns of a node
-// adjacent).  The work is split into (node, cell) pairs: along each direction
-// an internal node at patch coordinate p in 1..2k-1 lies in cell layer 0
-// (p <= k) and/or 1 (p >= k), which gives 2k (p, layer) choices per direction
-// and (2k)^d pairs per patch, enumerated arithmetically (pairs of absent nodes
-// or inactive cells contribute zero).  A pair applies its cell row (cut-cell
-// matrix or uncut stiffness, read once for all columns) and the ghost-face
-// terms of that cell (from the level's face buffer W, written by k_face_w for
-// the current x just before) to all columns, into parts[pair][column]; each
-// node then sums its 1..2^d pairs in a fixed order.  Every column follows the
-// same arithmetic in the same order, so its result does not depend on the
-// other columns.  Returns the residual rows in the LDS of the staged closure
-// (free once the pairs are formed): rs[i][c] = b_c - (A x_c) at node i for
-// i < nj and c < ncol, zero elsewhere in the first nrows rows (nrows <= the
-// closure's node count).  All threads of the block call it (it synchronises).
-template <int D, int K, typename T, int NCOL>
-struct PairSmem {
-  using S = Shape<D, K>;
-  static constexpr int NPAIR = Pow<2 * K, D>::v;
-  double tab[S::T_GC + K - S::T_D0];  // d0 | d1 | gc
-  T xs[S::NC][NCOL];
-  T parts[NPAIR][NCOL];
-  int16_t slot[S::NP];  // row of the patch's node at each internal position, -1 if absent
-  uint8_t cfl[1 << D], cgh[1 << D];
-  int32_t ccut[1 << D], cgid[1 << D];
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// One 16x16x4 matrix-core product: lane l holds A(l%16, l/16) and B(l/16,
+// l%16); of D it holds column l%16 and, as element v, row mfma_row(l, v).
+__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ doublex4 mfma16(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  using Acc = floatx4;
+  static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane / 16) + v; }
+};
+template <>
+struct Mfma<double> {
+  using Acc = doublex4;
+  static __device__ __forceinline__ int row(int lane, int v) { return 4 * v + lane / 16; }
 };
 
-template <int D, int K, typename T, int NCOL>
-__device__ void cut_residual_cols(const KLevel& L, const CutGroupDev& G, int gp, const T* __restrict__ x,
-                                  const T* __restrict__ b, const T* __restrict__ W, int ncol,
-                                  PairSmem<D, K, T, NCOL>& sm, int nrows, int& off, int& nj) {
+// Cut colour step for up to kMaxCols columns, one block per patch: residual
+// rows of all columns, dense local solve, and the update (two-buffer form, see
+// k_cut_solve) in one launch.
+//   1. x on the patch closure is staged in LDS, column by column.
+//   2. Cell rows on the matrix cores: every active cell of the patch
+//      multiplies the k^d rows of its matrix (cut-cell matrix or uncut
+//      stiffness) that belong to internal nodes with the cell's part of the
+//      closure, 16 rows x 4 nodes x (8 of 16) columns an instruction, so a
+//      matrix entry is loaded once for all columns and x comes out of LDS once
+//      per 16 rows.  A wave takes whole cells; its matrix loads do not depend
+//      on x and are issued before the closure has arrived.
+//   3. Ghost faces by sum factorisation: for a direction, the faces on the
+//      planes 0, 1, 2 of one tangential cell act on the node lines along the
+//      direction with the rank-k matrix sum_m gc_m j_m j_m^T (j_m: the jump of
+//      the m-th derivative as weights of the 2k+1 nodes), then with the 1-D
+//      mass in each tangential direction.  A wave takes one (direction,
+//      tangential cell), so whether a plane has a face is a scalar branch; a
+//      lane takes one node line of one column, and the tangential contractions
+//      exchange values between the 4 lanes of a quad and the 4 quads of a row
+//      of 16 lanes.  Faces on the patch boundary read their k node layers
+//      beyond the closure from memory.
+//   4. A thread sums, per (node, column), the cell rows and the ghost rows in
+//      a fixed order.
+//   5. d = A_j^{-1} r on the matrix cores; FP32 reads the inverse in tile
+//      order (CutGroupDev::inv_tiles), FP64 the symmetric dense inverse.
+// A column's arithmetic does not depend on the other columns or their number.
+// The former form (a jump pre-pass over all faces of the level, one thread per
+// cell row with 8 accumulators, a separate update) was bound by one patch's
+// serial chain and by LDS reads (one 8-column row of x per matrix entry).
+// Union of 8 spheres, Q3, 64^3 cells, 8 columns, FP32: finest step with jumps
+// and update 317 -> 150 us, V-cycle 23.0 -> 10.5 ms; bound by one patch's chain
+// of loads, LDS exchanges and dependent products at 4 blocks per CU (LDS).
+template <int D, int K, typename T, int NW_>
+struct ColsShape {
   using S = Shape<D, K>;
-  constexpr int N1 = S::N1, NL = S::NL, NC = S::NC, NC1 = S::NC1, NP1 = S::NP1, NCELL = 1 << D;
-  constexpr int NT = Pow<N1, D - 1>::v;
-  constexpr int NTAB = S::T_GC + K - S::T_D0;
-  constexpr int NPAIR = PairSmem<D, K, T, NCOL>::NPAIR;
-  constexpr int TH = CutShape<D, K>::THREADS;
+  static constexpr int NW = NW_;                         // waves per block
+  static constexpr int TH = 64 * NW;
+  static constexpr int NCELL = 1 << D;
+  static constexpr int KD = Pow<K, D>::v;                // internal rows per cell
+  static constexpr int NRT = (KD + 15) / 16;             // row tiles per cell
+  static constexpr bool VEC = S::NL % 16 == 0;           // cell rows in runs of 4 entries per lane
+  static constexpr int NKS = (S::NL + 3) / 4;            // matrix-core steps per row tile
+  static constexpr int NPAIR = Pow<2 * K, D>::v | 1;     // (node, cell) pairs, odd column stride
+  static constexpr int NPP = (S::NP + 15) / 16 * 16;     // residual rows, padded
+  static constexpr int HT = Pow<2 * K, D - 1>::v;        // (tangential cell, internal node) choices
+  static constexpr int HS = (S::NP1 * HT) | 1;           // ghost rows per direction and column, odd stride
+  static constexpr int LPC = D == 3 ? 16 : 4;            // lanes of one column in a ghost task
+  static constexpr int CPW = 64 / LPC;                   // columns of one ghost task
+  static constexpr int NGT = (kMaxCols + CPW - 1) / CPW; // ghost tasks per (direction, tangential cell)
+  static constexpr int NPT = S::NP <= 1 ? 1 : S::NP <= 4 ? 4 : S::NP <= 16 ? 16 : S::NP <= 32 ? 32 : S::NP <= 64 ? 64 : 128;
+  static constexpr int CPI = TH / NPT;                   // columns per round of (node, column) tasks
+  static constexpr int NRD = (kMaxCols + CPI - 1) / CPI; // rounds
+  static constexpr int COPY = 8;                         // copy-job items per thread of a copy block
+  // column of round u of a task with first column tc, kept in range where the task has none
+  static __device__ __forceinline__ int col(int tc, int u) {
+    const int c = tc + CPI * u;
+    return CPI * NRD > kMaxCols && c >= kMaxCols ? kMaxCols - 1 : c;
+  }
+};
+
+template <int D, int K, typename T, int NW>
+struct ColsSmem {
+  using S = Shape<D, K>;
+  using C = ColsShape<D, K, T, NW>;
+  T xs[kMaxCols][S::NC];             // x on the closure (the node count is odd)
+  T parts[kMaxCols][C::NPAIR];       // cell rows
+  T H[D][kMaxCols][C::HS];           // ghost rows
+  T rs[kMaxCols][C::NPP + 1];        // residual rows
+  T jm[K][2 * K + 1], gj[K][2 * K + 1], mh[S::N1][S::N1];  // jump weights j_m, gc_m j_m, 1-D mass
+  int32_t node[C::NPP];              // lattice node and closure index of every row
+  int16_t pos[C::NPP];
+};
+
+// The value that the DPP pattern CTRL brings to this lane: 0x55 q the lane q of
+// its quad, 0x120 + n the lane n below it in its row of 16 (cyclic).
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+template <int D, int K, typename T, int NW>
+__device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev& G, const T* __restrict__ x,
+                                              const T* __restrict__ b, T* __restrict__ dbuf, T* __restrict__ xb,
+                                              const CopyJob& cj, int ncol) {
+  using S = Shape<D, K>;
+  using C = ColsShape<D, K, T, NW>;
+  using Acc = typename Mfma<T>::Acc;
+  constexpr int N1 = S::N1, NL = S::NL, NC = S::NC, W1 = S::NC1, NP1 = S::NP1, KD = C::KD, NKS = C::NKS;
+  constexpr int NCELL = C::NCELL, TH = C::TH;
+  __shared__ ColsSmem<D, K, T, NW> sm;
   const int tid = threadIdx.x;
-  for (int i = tid; i < NTAB; i += TH) sm.tab[i] = L.tables[S::T_D0 + i];
-  for (int i = tid; i < S::NP; i += TH) sm.slot[i] = -1;
-  const double* d0 = sm.tab;
-  const double* d1 = sm.tab + K * N1;
-  const double* gc = sm.tab + 2 * K * N1;
-  off = G.off[gp];
-  nj = G.off[gp + 1] - off;
-  const int NV = L.N + 1;
+  if ((int)blockIdx.x < cj.nblk) {
+    // copy block (see k_cut_solve): the items once for all columns
+#pragma unroll
+    for (int u = 0; u < C::COPY; ++u) {
+      const int64_t i = ((int64_t)blockIdx.x * C::COPY + u) * TH + tid;
+      if (i >= cj.n || (cj.skip[i] & cj.mask)) continue;
+      const int64_t nd = cj.nodes[i];
+      for (int c = 0; c < ncol; ++c) xb[c * L.n_nodes + nd] = x[c * L.n_nodes + nd];
+    }
+    return;
+  }
+  if ((int)blockIdx.x - cj.nblk >= G.n_patch) return;  // grouped launches: a block beyond this problem's work
+  const int gp = xcd_block(blockIdx.x - cj.nblk, G.n_patch);
+  const int lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int lr = lane % 16, lk = lane / 16;
+  const int off = G.off[gp], nj = G.off[gp + 1] - off;
+  const int64_t nn = L.nn, nn2 = nn * nn;
   int V[3] = {0, 0, 0};
   {
     int vr = G.vertex[gp];
+    const int NV = L.N + 1;
 #pragma unroll
     for (int a = 0; a < D; ++a) { V[a] = vr % NV; vr /= NV; }
   }
-  const int64_t nn = L.nn, nn2 = nn * nn;
   const int64_t cbase = K * (V[0] - 1) + nn * (K * (V[1] - 1)) + (D == 3 ? nn2 * (K * (V[2] - 1)) : 0);
-  if (tid < NCELL) {
-    int c[3];
-    bool in = true;
+  // local index of row r (of the k^d internal rows of cell o), and its pair index
+  auto row_of = [&](int o, int r, int& iloc, int& pair) {
+    iloc = 0;
+    pair = 0;
+    int s1 = 1, s2 = 1;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      c[a] = V[a] - 1 + ((tid >> a) & 1);
-      in = in && c[a] >= 0 && c[a] < L.N;
+      const int i = r % K, layer = (o >> a) & 1;
+      r /= K;
+      iloc += (i + 1 - layer) * s1;
+      pair += (layer * K + i) * s2;
+      s1 *= N1;
+      s2 *= 2 * K;
     }
-    uint8_t f = 0, g = 0;
-    int32_t cid = -1, gid = -1;
-    if (in) {
-      const int64_t cl = cell_lin(D, L.N, c);
-      f = L.flags[cl];
-      g = L.ghost[cl];
-      cid = L.cut_id[cl];
-      gid = L.cell_gid[cl];
+  };
+  // matrix entries of the wave's cell o for one row tile: VEC: lane (lr, lk)
+  // holds nodes 16 kk + 4 lk + s (kk, s < 4) of row lr, used in step 4 kk + s;
+  // else node 4 ks + lk in step ks
+  auto load_rows = [&](int rt, uint16_t fg, int cut, T* a, int o) {
+    const int r = rt * 16 + lr;
+    int iloc, pair;
+    row_of(o, r < KD ? r : KD - 1, iloc, pair);
+    const T* m = (fg & 2) ? L.cut_mats_t<T>() + (int64_t)cut * NL * NL : L.kcell_t<T>() + S::T_KCELL;
+    m += iloc * NL;
+    if constexpr (C::VEC) {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) a[ks] = m[16 * (ks / 4) + 4 * lk + ks % 4];
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        const int q = 4 * ks + lk;
+        a[ks] = q < NL ? m[q] : (T)0;
+      }
     }
-    sm.cfl[tid] = f;
-    sm.cgh[tid] = g;
-    sm.ccut[tid] = cid;
-    sm.cgid[tid] = gid;
+  };
+  auto node_of = [&](int ks) { return C::VEC ? 16 * (ks / 4) + 4 * lk + ks % 4 : 4 * ks + lk; };
+  // products of one row tile, the rows stored as pairs
+  auto mul_rows = [&](int o, int rt, const T* a) {
+    int xo = K * (o & 1) + W1 * K * ((o >> 1) & 1);
+    if (D == 3) xo += W1 * W1 * K * ((o >> 2) & 1);
+    const T* xc = sm.xs[lr % kMaxCols] + xo;
+    Acc acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      const int q = node_of(ks), b12 = q / N1;
+      const int xi = q % N1 + W1 * (b12 % N1) + (D == 3 ? W1 * W1 * (b12 / N1) : 0);
+      const T bb = q < NL ? xc[xi] : (T)0;
+      acc = mfma16(a[ks], bb, acc);
+    }
+    if (lr < kMaxCols) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = rt * 16 + Mfma<T>::row(lane, v);
+        if (r < KD) {
+          int iloc, pair;
+          row_of(o, r, iloc, pair);
+          sm.parts[lr][pair] = acc[v];
+        }
+      }
+    }
+  };
+  // the wave's cells: flags, and matrix loads in flight while x is staged (the
+  // first cell only where all of them would take more than 64 registers)
+  constexpr int NCW = NCELL / NW;
+  constexpr bool ALL = NCW * C::NRT * NKS * (int)sizeof(T) <= 64 * 4;
+  uint64_t fgq[NCELL / 4];  // flags of the 2^d cells, 4 cells a word (scalar loads)
+#pragma unroll
+  for (int i = 0; i < NCELL / 4; ++i)
+    fgq[i] = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4) + i];
+  auto cell_fg = [&](int o) { return static_cast<int>(((NCELL > 4 && o >= 4) ? fgq[NCELL / 4 - 1] : fgq[0]) >> (16 * (o & 3))) & 0xffff; };
+  int fg[NCW], cut[NCW];
+  T am[ALL ? NCW : 1][C::NRT][NKS];
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    fg[i] = cell_fg(i * NW + wave);
+    cut[i] = G.cell_cut[(int64_t)gp * NCELL + i * NW + wave];
   }
-  // node, patch position and b of the thread's row, fetched before the staging
+#pragma unroll
+  for (int i = 0; i < (ALL ? NCW : 1); ++i)
+    if (fg[i] & 1) {
+#pragma unroll
+      for (int rt = 0; rt < C::NRT; ++rt) load_rows(rt, fg[i], cut[i], am[i][rt], i * NW + wave);
+    }
+  {
+    // closure of every column; nodes outside the lattice are zero
+    constexpr int NIT = (NC * kMaxCols + TH - 1) / TH;
+    constexpr int UB = NIT < 16 ? NIT : 16;
+    for (int u0 = 0; u0 < NIT; u0 += UB) {
+      if (u0 * TH >= NC * ncol) break;
+      T v[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int e = tid + TH * (u0 + u);
+        v[u] = 0;
+        if (e < NC * ncol) {
+          const int c = e / NC, q = e % NC;
+          const int q0 = q % W1, q1 = (q / W1) % W1, q2 = q / (W1 * W1);
+          const int I0 = K * (V[0] - 1) + q0, I1 = K * (V[1] - 1) + q1, I2 = D == 3 ? K * (V[2] - 1) + q2 : 0;
+          const bool in = I0 >= 0 && I0 < nn && I1 >= 0 && I1 < nn && (D == 2 || (I2 >= 0 && I2 < nn));
+          if (in) v[u] = x[c * L.n_nodes + cbase + q0 + nn * q1 + (D == 3 ? nn2 * q2 : 0)];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int e = tid + TH * (u0 + u);
+        if (e < NC * kMaxCols) (&sm.xs[0][0])[e] = v[u];
+      }
+    }
+    for (int e = NC * ncol + tid; e < NC * kMaxCols; e += TH) (&sm.xs[0][0])[e] = 0;
+  }
+  // level tables: mass, jump weights j_m(s) and gc_m j_m(s)
+  for (int t = tid; t < N1 * N1; t += TH) (&sm.mh[0][0])[t] = (T)L.tables[S::T_MHAT + t];
+  for (int t = tid; t < K * (2 * K + 1); t += TH) {
+    const int m = t / (2 * K + 1), s = t % (2 * K + 1);
+    double j = 0.0;
+    if (s <= K) j += L.tables[S::T_D1 + m * N1 + s];
+    if (s >= K) j -= L.tables[S::T_D0 + m * N1 + (s - K)];
+    sm.jm[m][s] = (T)j;
+    sm.gj[m][s] = (T)(L.tables[S::T_GC + m] * j);
+  }
+  // (node, column) task of the thread: row ti, columns tc + CPI u
+  const int ti = tid % C::NPT, tc = tid / C::NPT;
   int pi[3] = {0, 0, 0};
-  T bv[NCOL];
+  T bv[C::NRD];
+  if (ti < nj) {
+    const int node = G.nodes[off + ti];
 #pragma unroll
-  for (int c = 0; c < NCOL; ++c) bv[c] = 0;
-  if (tid < nj) {
-    const int node = G.nodes[off + tid];
-#pragma unroll
-    for (int c = 0; c < NCOL; ++c)
-      if (c < ncol) bv[c] = b[c * L.n_nodes + node];
+    for (int u = 0; u < C::NRD; ++u) {
+      const int c = tc + C::CPI * u;
+      bv[u] = c < ncol ? b[c * L.n_nodes + node] : (T)0;
+    }
     int r = node;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
       pi[a] = r % L.nn - K * (V[a] - 1);
       r /= L.nn;
     }
-  }
-  // stage the closure of every column (nodes outside the lattice are zero);
-  // all loads of a thread are issued before its LDS stores
-  {
-    constexpr int NST = NC * NCOL;
-    constexpr int NIT = (NST + TH - 1) / TH;
-    T v[NIT];
-#pragma unroll
-    for (int u = 0; u < NIT; ++u) {
-      const int e = tid + TH * u;
-      v[u] = 0;
-      const int q = e / NCOL, c = e % NCOL;
-      if (e < NST && c < ncol) {
-        const int q0 = q % NC1, q1 = (q / NC1) % NC1, q2 = q / (NC1 * NC1);
-        const int I0 = K * (V[0] - 1) + q0, I1 = K * (V[1] - 1) + q1, I2 = D == 3 ? K * (V[2] - 1) + q2 : 0;
-        const bool in = I0 >= 0 && I0 < nn && I1 >= 0 && I1 < nn && (D == 2 || (I2 >= 0 && I2 < nn));
-        if (in) v[u] = x[c * L.n_nodes + cbase + q0 + nn * q1 + (D == 3 ? nn2 * q2 : 0)];
-      }
+    if (tc == 0) {
+      sm.node[ti] = node;
+      sm.pos[ti] = static_cast<int16_t>(pi[0] + W1 * pi[1] + (D == 3 ? W1 * W1 * pi[2] : 0));
     }
-#pragma unroll
-    for (int u = 0; u < NIT; ++u) {
-      const int e = tid + TH * u;
-      if (e < NST) sm.xs[e / NCOL][e % NCOL] = v[u];
-    }
-  }
-  if (tid < nj) {
-    int pos = 0;
-#pragma unroll
-    for (int a = D - 1; a >= 0; --a) pos = pos * NP1 + (pi[a] - 1);
-    sm.slot[pos] = static_cast<int16_t>(tid);
   }
   __syncthreads();
-  const int64_t wcol = L.n_faces * K * NT;
-  for (int t = tid; t < NPAIR; t += TH) {
-    int p[3], o = 0, pos = 0;
-    {
-      int r = t;
+  // cell rows
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const int j = r % (2 * K);
-        r /= 2 * K;
-        const int layer = j >= K ? 1 : 0;
-        p[a] = j < K ? j + 1 : j;
-        o |= layer << a;
+  for (int i = 0; i < NCW; ++i) {
+    const int o = i * NW + wave;
+    if (fg[i] & 1) {
+      if (!ALL && i > 0) {
+#pragma unroll
+        for (int rt = 0; rt < C::NRT; ++rt) load_rows(rt, fg[i], cut[i], am[0][rt], o);
       }
 #pragma unroll
-      for (int a = D - 1; a >= 0; --a) pos = pos * NP1 + (p[a] - 1);
-    }
-    T acc[NCOL];
-#pragma unroll
-    for (int c = 0; c < NCOL; ++c) acc[c] = 0;
-    const uint8_t f = sm.cfl[o];
-    if (sm.slot[pos] >= 0 && (f & 1)) {
-      int il[3];
-#pragma unroll
-      for (int a = 0; a < D; ++a) il[a] = p[a] - K * ((o >> a) & 1);
-      int iloc = il[0] + N1 * il[1];
-      if (D == 3) iloc += N1 * N1 * il[2];
-      int qb = K * (o & 1) + NC1 * K * ((o >> 1) & 1);  // closure index of the cell's first node
-      if (D == 3) qb += NC1 * NC1 * K * ((o >> 2) & 1);
-      if (f & 2) {
-        const T* row = L.cut_mats_t<T>() + ((int64_t)sm.ccut[o] * NL + iloc) * NL;
-#pragma unroll 8
-        for (int bq = 0; bq < NL; ++bq) {
-          const int b0 = bq % N1, b12 = bq / N1;
-          const int q = qb + b0 + NC1 * (b12 % N1) + (D == 3 ? NC1 * NC1 * (b12 / N1) : 0);
-          const T m = row[bq];
-#pragma unroll
-          for (int c = 0; c < NCOL; ++c) acc[c] += m * sm.xs[q][c];
-        }
-      } else {
-        const T* row = L.kcell_t<T>() + S::T_KCELL + iloc * NL;
-#pragma unroll 8
-        for (int bq = 0; bq < NL; ++bq) {
-          const int b0 = bq % N1, b12 = bq / N1;
-          const int q = qb + b0 + NC1 * (b12 % N1) + (D == 3 ? NC1 * NC1 * (b12 / N1) : 0);
-          const T m = row[bq];
-#pragma unroll
-          for (int c = 0; c < NCOL; ++c) acc[c] += m * sm.xs[q][c];
-        }
-      }
-      const uint8_t g = sm.cgh[o];
-      if (g) {
-        const int gid = sm.cgid[o];
-#pragma unroll
-        for (int dir = 0; dir < D; ++dir)
-#pragma unroll
-          for (int side = 0; side < 2; ++side) {
-            if (!(g & (1 << (2 * dir + side)))) continue;
-            const int fid = L.cell_faces[(int64_t)gid * 2 * D + 2 * dir + side];
-            int it = 0, st = 1;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-              if (a == dir) continue;
-              it += il[a] * st;
-              st *= N1;
-            }
-            const T* w = W + (int64_t)fid * K * NT + it;
-#pragma unroll
-            for (int m = 0; m < K; ++m) {
-              const T sg = (T)(gc[m] * (side == 1 ? d1[m * N1 + il[dir]] : -d0[m * N1 + il[dir]]));
-#pragma unroll
-              for (int c = 0; c < NCOL; ++c)
-                if (c < ncol) acc[c] += sg * w[c * wcol + m * NT];
-            }
-          }
+      for (int rt = 0; rt < C::NRT; ++rt) mul_rows(o, rt, am[ALL ? i : 0][rt]);
+    } else {
+      for (int e = lane; e < KD * kMaxCols; e += 64) {
+        int iloc, pair;
+        row_of(o, e % KD, iloc, pair);
+        sm.parts[e / KD][pair] = 0;
       }
     }
-#pragma unroll
-    for (int c = 0; c < NCOL; ++c) sm.parts[t][c] = acc[c];
   }
-  __syncthreads();
-  if (tid < nj) {
-    // the node's pairs: per direction index j = p - 1 (layer 0, p <= k) and
-    // j = p (layer 1, p >= k), in increasing pair index
-    int jlo[3], jn[3];
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      jlo[a] = pi[a] <= K ? pi[a] - 1 : pi[a];
-      jn[a] = pi[a] == K ? 2 : 1;
-    }
-    T acc[NCOL];
-#pragma unroll
-    for (int c = 0; c < NCOL; ++c) acc[c] = 0;
-    const int ncomb = jn[0] * jn[1] * (D == 3 ? jn[2] : 1);
-    for (int comb = 0; comb < ncomb; ++comb) {
-      int t = 0, r = comb, st = 1;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const int sel = r % jn[a];
-        r /= jn[a];
-        t += (jlo[a] + sel) * st;
-        st *= 2 * K;
-      }
-#pragma unroll
-      for (int c = 0; c < NCOL; ++c) acc[c] += sm.parts[t][c];
-    }
-    T(*rs)[NCOL] = sm.xs;
-#pragma unroll
-    for (int c = 0; c < NCOL; ++c) rs[tid][c] = c < ncol ? bv[c] - acc[c] : (T)0;
-  }
-  for (int e = nj * NCOL + tid; e < nrows * NCOL; e += TH) (&sm.xs[0][0])[e] = 0;
-  __syncthreads();
-}
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// Cut patches, phase 1 for up to kMaxCols columns in FP32, local solves on the
-// matrix cores.  Residuals of all columns by cut_residual_cols, then
-// D = A_j^{-1} R with v_mfma_f32_16x16x4f32, which multiplies a 16x4 tile of
-// the inverse (lane l holds row l%16, column l/16) by a 4x16 slice of R (lane
-// l holds row l/16, column l%16; columns >= kMaxCols are zero) into 16x16
-// accumulators (lane l holds rows 4(l/16)..4(l/16)+3 of column l%16).  The
-// inverse is stored tile by tile in exactly that lane order
-// (CutGroupDev::inv_tiles), so a tile is one coalesced 256-byte wave load, and
-// it is read once for all columns.  Row blocks of 16 are spread over the
-// block's wavefronts.
-template <int D, int K>
-__device__ __forceinline__ void cut_solve_mfma_body(KLevel L, CutGroupDev G, const float* __restrict__ x,
-                                                    const float* __restrict__ b, const float* __restrict__ W,
-                                                    float* __restrict__ dbuf, int ncol) {
-  using S = Shape<D, K>;
-  constexpr int NPK = (S::NP + 3) / 4 * 4;
-  __shared__ PairSmem<D, K, float, kMaxCols> sm;
-  static_assert(NPK <= S::NC, "the residual rows fit in the staged closure");
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int gp = xcd_block(blockIdx.x, gridDim.x);
-  if (gp >= G.n_patch) return;  // grouped launches: a block beyond this problem's patches
-  int off, nj;
-  cut_residual_cols<D, K, float, kMaxCols>(L, G, gp, x, b, W, ncol, sm, NPK, off, nj);
-  // residual columns; rows >= nj and columns >= ncol are zero
-  const float(*rs)[kMaxCols] = sm.xs;
-  const int lane = tid % 64, wave = tid / 64, nwave = nth / 64;
+  // the first row block of the inverse: its loads do not depend on the residual
   const int nrb = (nj + 15) / 16, nkb = (nj + 3) / 4;
-  const int kr = lane / 16, jc = lane % 16;
-  const float* tiles = G.inv_tiles + G.tile_off[gp];
-  // all tiles of a row block are loaded at once (NKB <= 32 registers), then
-  // the MFMA chain runs on them
-  constexpr int NKB = NPK / 4;
-  for (int rb = wave; rb < nrb; rb += nwave) {  // wave-uniform: every lane takes part in the MFMA
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    const float* t = tiles + (int64_t)rb * nkb * 64 + lane;
-    float a[NKB];
+  constexpr int NKB = (S::NP + 3) / 4;
+  auto load_inv = [&](int rb, T* a) {
+    if constexpr (sizeof(T) == 4) {
+      const float* t = G.inv_tiles + G.tile_off[gp] + (int64_t)rb * nkb * 64 + lane;
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) a[kb] = kb < nkb ? t[kb * 64] : 0.f;
+      for (int kb = 0; kb < NKB; ++kb) a[kb] = kb < nkb ? t[kb * 64] : 0.f;
+    } else {
+      // rows of the symmetric inverse as columns: 16 consecutive entries
+      const int i = rb * 16 + lr;
+      const double* inv = G.inv_t<double>() + G.inv_off[gp] + (i < nj ? i : nj - 1);
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      if (kb < nkb) {
-        const float bb = jc < kMaxCols ? rs[kb * 4 + kr][jc] : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kb], bb, acc, 0, 0, 0);
+      for (int kb = 0; kb < NKB; ++kb) {
+        const int j = 4 * kb + lk;
+        a[kb] = j < nj ? inv[(int64_t)j * nj] : 0.0;
       }
     }
-    if (jc < ncol) {
+  };
+  T ai[NKB];
+  if (wave < nrb) load_inv(wave, ai);
+  // ghost rows; bit dir 2^(D-1) + t of gmask: that (direction, tangential cell) has a face
+  constexpr int NTC = 1 << (D - 1);
+  uint32_t gmask = 0;
+#pragma unroll
+  for (int dt = 0; dt < D * NTC; ++dt) {
+    const int dir = dt / NTC, t = dt % NTC;
+    const int d0 = dir == 0 ? 1 : 0, d1 = dir == 2 ? 1 : 2;  // tangential directions (d1: 3-D only)
+    const int o = ((t & 1) << d0) | (D == 3 ? (t >> 1) << d1 : 0);
+    const int glo = cell_fg(o) >> 8, ghi = cell_fg(o | 1 << dir) >> 8;
+    if ((glo & (3 << (2 * dir))) || (ghi & (2 << (2 * dir)))) gmask |= 1u << dt;
+  }
+  auto ghost = [&](int dt, int c) {
+    const int dir = dt / NTC, t0 = dt & 1, t1 = D == 3 ? (dt >> 1) & 1 : 0;
+    const int d0 = dir == 0 ? 1 : 0, d1 = dir == 2 ? 1 : 2;
+    const int o = (t0 << d0) | (D == 3 ? t1 << d1 : 0);
+    const int glo = cell_fg(o) >> 8, ghi = cell_fg(o | 1 << dir) >> 8;
+    const bool f0 = glo & (1 << (2 * dir)), f1 = glo & (2 << (2 * dir)), f2 = ghi & (2 << (2 * dir));
+    const int b0 = lane % 4, b1 = D == 3 ? (lane / 4) % 4 : 0;
+    const bool on = ((gmask >> dt) & 1) && c < ncol && b0 < N1 && b1 < N1;
+    T y[NP1];
+#pragma unroll
+    for (int p = 0; p < NP1; ++p) y[p] = 0;
+    if (on) {
+      const int sd = dir == 0 ? 1 : dir == 1 ? W1 : W1 * W1;
+      const int s0 = d0 == 0 ? 1 : W1, s1 = D == 3 ? (d1 == 1 ? W1 : W1 * W1) : 0;
+      const T* xl = sm.xs[c] + (K * t0 + b0) * s0 + (K * t1 + b1) * s1;
+      const int64_t gd = dir == 0 ? 1 : dir == 1 ? nn : nn2, g0 = d0 == 0 ? 1 : nn, g1 = D == 3 ? (d1 == 1 ? nn : nn2) : 0;
+      const T* xg = x + c * L.n_nodes + cbase + (K * t0 + b0) * g0 + (K * t1 + b1) * g1;
+      T lo[K], hi[K], xv[2 * K + 1];  // node layers beyond the closure, and in it
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        lo[q] = f0 ? xg[(q - K) * gd] : (T)0;
+        hi[q] = f2 ? xg[(2 * K + 1 + q) * gd] : (T)0;
+      }
+#pragma unroll
+      for (int q = 0; q <= 2 * K; ++q) xv[q] = xl[q * sd];
+#pragma unroll
+      for (int m = 0; m < K; ++m) {
+        T jm[2 * K + 1], gj[2 * K + 1];
+#pragma unroll
+        for (int q = 0; q <= 2 * K; ++q) {
+          jm[q] = sm.jm[m][q];
+          gj[q] = sm.gj[m][q];
+        }
+        if (f1) {
+          T J = 0;
+#pragma unroll
+          for (int q = 0; q <= 2 * K; ++q) J += jm[q] * xv[q];
+#pragma unroll
+          for (int p = 1; p < 2 * K; ++p) y[p - 1] += gj[p] * J;
+        }
+        if (f0) {
+          T J = 0;
+#pragma unroll
+          for (int q = 0; q < K; ++q) J += jm[q] * lo[q];
+#pragma unroll
+          for (int q = K; q <= 2 * K; ++q) J += jm[q] * xv[q - K];
+#pragma unroll
+          for (int p = 1; p <= K; ++p) y[p - 1] += gj[p + K] * J;
+        }
+        if (f2) {
+          T J = 0;
+#pragma unroll
+          for (int q = 0; q <= K; ++q) J += jm[q] * xv[q + K];
+#pragma unroll
+          for (int q = K + 1; q <= 2 * K; ++q) J += jm[q] * hi[q - K - 1];
+#pragma unroll
+          for (int p = K; p < 2 * K; ++p) y[p - 1] += gj[p - K] * J;
+        }
+      }
+    }
+    // 1-D masses in the tangential directions: row b0 over the lanes of the
+    // quad, then row b1 over the quads of the 16 lanes (idle lanes hold zeros)
+    T w0[4], w1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int q1 = (b1 - q) & 3;  // quad that a rotation by 4 q lanes brings here
+      w0[q] = b0 < N1 && q < N1 ? sm.mh[b0][q < N1 ? q : 0] : (T)0;
+      w1[q] = D == 3 && b1 < N1 && q1 < N1 ? sm.mh[b1][q1] : (T)0;
+    }
+    const int i0 = b0 - 1 + t0, i1 = b1 - 1 + t1;  // internal rows 0..k-1 of the tangential cell
+    const bool put = on && i0 >= 0 && i0 < K && (D == 2 || (i1 >= 0 && i1 < K));
+    T* h = sm.H[dir][c < kMaxCols ? c : 0] + (D == 3 ? (t0 * K + i0) * 2 * K + t1 * K + i1 : t0 * K + i0);
+#pragma unroll
+    for (int p = 0; p < NP1; ++p) {
+      T v = w0[0] * lane_dpp<0x00>(y[p]) + w0[1] * lane_dpp<0x55>(y[p]);
+      if (N1 > 2) v += w0[2] * lane_dpp<0xaa>(y[p]);
+      if (N1 > 3) v += w0[3] * lane_dpp<0xff>(y[p]);
+      if (D == 3)
+        v = (w1[0] * v + w1[1] * lane_dpp<0x124>(v)) + (w1[2] * lane_dpp<0x128>(v) + w1[3] * lane_dpp<0x12c>(v));
+      if (put) h[p * C::HT] = v;
+    }
+  };
+  if (ncol > C::CPW / 2) {
+    // a wave per (direction, tangential cell) and CPW columns: the faces are scalar
+    for (int wt = wave; wt < D * NTC * C::NGT; wt += NW) {
+      const int dt = wt / C::NGT, c0 = (wt % C::NGT) * C::CPW;
+      if (((gmask >> dt) & 1) && c0 < ncol) ghost(dt, c0 + lane / C::LPC);
+    }
+  } else {
+    // few columns: several (direction, tangential cell) choices side by side in a wave
+    const int ns = D * NTC * ncol;
+    for (int wt = wave; wt * C::CPW < ns; wt += NW) {
+      const int slot = wt * C::CPW + lane / C::LPC;
+      ghost(slot < ns ? slot / ncol : 0, slot < ns ? slot % ncol : kMaxCols);
+    }
+  }
+  __syncthreads();
+  // residual rows; rows beyond the patch and columns beyond ncol are zero
+  {
+    T acc[C::NRD];
+#pragma unroll
+    for (int u = 0; u < C::NRD; ++u) acc[u] = 0;
+    if (ti < nj && tc < ncol) {
+      // the node's pairs: per direction index j = p - 1 (layer 0, p <= k) and
+      // j = p (layer 1, p >= k)
+      int jlo[3] = {0, 0, 0}, jn[3] = {1, 1, 1};
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        jlo[a] = pi[a] <= K ? pi[a] - 1 : pi[a];
+        jn[a] = pi[a] == K ? 2 : 1;
+      }
+      // every choice of layers is read, so that the reads are in flight together;
+      // those that the node does not have (and unwritten ghost rows) are dropped
+#pragma unroll
+      for (int e = 0; e < NCELL; ++e) {
+        int t = 0, st = 1;
+        bool has = true;
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          const int ea = (e >> a) & 1;
+          has = has && ea < jn[a];
+          t += (jlo[a] + (ea & (jn[a] - 1))) * st;
+          st *= 2 * K;
+        }
+#pragma unroll
+        for (int u = 0; u < C::NRD; ++u) {
+          const T v = sm.parts[C::col(tc, u)][t];
+          acc[u] += has ? v : (T)0;
+        }
+      }
+#pragma unroll
+      for (int dir = 0; dir < D; ++dir) {
+        constexpr int D1[3] = {2, 2, 1};
+        const int d0 = dir == 0 ? 1 : 0, d1 = D1[dir];
+#pragma unroll
+        for (int e = 0; e < NTC; ++e) {
+          const int e0 = e & 1, e1 = e >> 1;
+          const int j0 = jlo[d0] + (e0 & (jn[d0] - 1)), j1 = D == 3 ? jlo[d1] + (e1 & (jn[d1] - 1)) : 0;
+          const int t = (j0 >= K ? 1 : 0) | (j1 >= K ? 2 : 0);
+          const bool has = e0 < jn[d0] && (D == 2 || e1 < jn[d1]) && ((gmask >> (dir * NTC + t)) & 1);
+          const int at = (pi[dir] - 1) * C::HT + (D == 3 ? j0 * 2 * K + j1 : j0);
+#pragma unroll
+          for (int u = 0; u < C::NRD; ++u) {
+            const T v = sm.H[dir][C::col(tc, u)][at];
+            acc[u] += has ? v : (T)0;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < C::NRD; ++u) {
+      const int c = tc + C::CPI * u;
+      if (c < kMaxCols && ti < C::NPP) sm.rs[c][ti] = ti < nj && c < ncol ? bv[u] - acc[u] : (T)0;
+    }
+  }
+  if constexpr (C::NPT < C::NPP) {
+    for (int e = tid; e < kMaxCols * (C::NPP - C::NPT); e += TH)
+      sm.rs[e / (C::NPP - C::NPT)][C::NPT + e % (C::NPP - C::NPT)] = 0;
+  }
+  __syncthreads();
+  for (int rb = wave; rb < nrb; rb += NW) {  // wave-uniform: every lane takes part in the products
+    if (rb != wave) load_inv(rb, ai);
+    Acc d = {0, 0, 0, 0};
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+      if (kb < nkb) d = mfma16(ai[kb], sm.rs[lr % kMaxCols][4 * kb + lk], d);
+    if (lr < ncol) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int i = rb * 16 + 4 * kr + v;
-        if (i < nj) dbuf[jc * G.n_nodes + off + i] = acc[v];
+        const int i = rb * 16 + Mfma<T>::row(lane, v);
+        if (i >= nj) continue;
+        if (xb)
+          xb[lr * L.n_nodes + sm.node[i]] = sm.xs[lr][sm.pos[i]] + d[v];
+        else
+          dbuf[lr * G.n_nodes + off + i] = d[v];
       }
     }
   }
 }
 
-template <int D, int K>
-__global__ __launch_bounds__((CutShape<D, K>::THREADS)) void k_cut_solve_mfma(KLevel L, CutGroupDev G,
-                                                                              const float* __restrict__ x,
-                                                                              const float* __restrict__ b,
-                                                                              const float* __restrict__ W,
-                                                                              float* __restrict__ dbuf, int ncol) {
-  cut_solve_mfma_body<D, K>(L, G, x, b, W, dbuf, ncol);
+template <int D, int K, typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void k_cut_cols(KLevel L, CutGroupDev G, const T* __restrict__ x,
+                                                      const T* __restrict__ b, T* __restrict__ dbuf,
+                                                      T* __restrict__ xb, CopyJob cj, int ncol) {
+  cut_cols_body<D, K, T, NW>(L, G, x, b, dbuf, xb, cj, ncol);
 }
 
-// argument record of k_cut_solve_mfma for grouped launches (k_grouped)
-template <int D, int K>
-struct CutSolveMfmaArgs {
+// argument record of k_cut_cols for grouped launches (k_grouped)
+template <int D, int K, typename T, int NW>
+struct CutColsArgs {
   KLevel L;
   CutGroupDev G;
-  const float* x;
-  const float* b;
-  const float* W;
-  float* dbuf;
+  const T* x;
+  const T* b;
+  T* dbuf;
+  T* xb;
+  CopyJob cj;
   int ncol;
-  __device__ void run() const { cut_solve_mfma_body<D, K>(L, G, x, b, W, dbuf, ncol); }
-};
-
-// Cut patches, phase 1 for up to kMaxCols columns in FP64: residuals of all
-// columns by cut_residual_cols (every cell row read once for all columns),
-// then d = A_j^{-1} r for all columns with the inverse read once: thread i
-// takes row i (= column i, the inverse is symmetric) and multiplies each entry
-// into every column's accumulator.  Column c's arithmetic (residual, then the
-// row sum in increasing j) does not depend on the other columns.
-template <int D, int K>
-__device__ __forceinline__ void cut_solve_cols_body(KLevel L, CutGroupDev G, const double* __restrict__ x,
-                                                    const double* __restrict__ b, const double* __restrict__ W,
-                                                    double* __restrict__ dbuf, int ncol) {
-  using S = Shape<D, K>;
-  constexpr int NB = 8;                        // independent inverse loads in flight per thread
-  constexpr int NPB = (S::NP + NB - 1) / NB * NB;
-  __shared__ PairSmem<D, K, double, kMaxCols> sm;
-  static_assert(NPB <= S::NC, "the residual rows fit in the staged closure");
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int gp = xcd_block(blockIdx.x, gridDim.x);
-  if (gp >= G.n_patch) return;  // grouped launches: a block beyond this problem's patches
-  int off, nj;
-  cut_residual_cols<D, K, double, kMaxCols>(L, G, gp, x, b, W, ncol, sm, NPB, off, nj);
-  const double(*rs)[kMaxCols] = sm.xs;  // rows >= nj and columns >= ncol are zero
-  const double* inv = G.inv_t<double>() + G.inv_off[gp];
-  for (int i = tid; i < nj; i += nth) {
-    double acc[kMaxCols];
-#pragma unroll
-    for (int c = 0; c < kMaxCols; ++c) acc[c] = 0.0;
-    for (int j = 0; j < nj; j += NB) {
-      double v[NB];
-      // loads past the last row re-read it; their residual rows are zero
-#pragma unroll
-      for (int u = 0; u < NB; ++u) v[u] = inv[(int64_t)(j + u < nj ? j + u : nj - 1) * nj + i];
-#pragma unroll
-      for (int u = 0; u < NB; ++u)
-#pragma unroll
-        for (int c = 0; c < kMaxCols; ++c) acc[c] += v[u] * rs[j + u][c];
-    }
-#pragma unroll
-    for (int c = 0; c < kMaxCols; ++c)
-      if (c < ncol) dbuf[c * G.n_nodes + off + i] = acc[c];
-  }
-}
-
-template <int D, int K>
-__global__ __launch_bounds__((CutShape<D, K>::THREADS)) void k_cut_solve_cols(KLevel L, CutGroupDev G,
-                                                                              const double* __restrict__ x,
-                                                                              const double* __restrict__ b,
-                                                                              const double* __restrict__ W,
-                                                                              double* __restrict__ dbuf, int ncol) {
-  cut_solve_cols_body<D, K>(L, G, x, b, W, dbuf, ncol);
-}
-
-// argument record of k_cut_solve_cols for grouped launches (k_grouped)
-template <int D, int K>
-struct CutSolveColsArgs {
-  KLevel L;
-  CutGroupDev G;
-  const double* x;
-  const double* b;
-  const double* W;
-  double* dbuf;
-  int ncol;
-  __device__ void run() const { cut_solve_cols_body<D, K>(L, G, x, b, W, dbuf, ncol); }
+  __device__ void run() const { cut_cols_body<D, K, T, NW>(L, G, x, b, dbuf, xb, cj, ncol); }
 };
 
 // dst = src on a node list (the cut region before a run of two-buffer cut steps).
 template <typename T>
-__global__ __launch_bounds__(256) void k_copy_nodes(const int32_t* __restrict__ nodes, int64_t n,
-                                                    const T* __restrict__ src, T* __restrict__ dst, int64_t ld) {
+__device__ __forceinline__ void copy_nodes_body(const int32_t* __restrict__ nodes, int64_t n,
+                                                const T* __restrict__ src, T* __restrict__ dst, int64_t ld) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e < n) {
     const int64_t o = blockIdx.y * ld + nodes[e];
     dst[o] = src[o];
   }
 }
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_copy_nodes(const int32_t* __restrict__ nodes, int64_t n,
+                                                    const T* __restrict__ src, T* __restrict__ dst, int64_t ld) {
+  copy_nodes_body<T>(nodes, n, src, dst, ld);
+}
+
+// argument record of k_copy_nodes for grouped launches (k_grouped)
+template <typename T>
+struct CopyNodesArgs {
+  const int32_t* nodes;
+  int64_t n;
+  const T* src;
+  T* dst;
+  int64_t ld;
+  __device__ void run() const { copy_nodes_body<T>(nodes, n, src, dst, ld); }
+};
 
 // Cut patches, phase 2: x[I_j] += d_j for all patches of the colour.
 template <typename T>
@@ -2397,52 +2574,44 @@ template <typename T>
 hipError_t launch_copy_nodes(const int32_t* nodes, int64_t n, const T* src, T* dst, int64_t ld, hipStream_t s,
                              int ncol) {
   if (n == 0) return hipSuccess;
-  if (record_none()) return hipSuccess;
+  if (record<256>(dim3(blocks(n), ncol), dim3(256), dev::CopyNodesArgs<T>{nodes, n, src, dst, ld})) return hipSuccess;
   hipLaunchKernelGGL((dev::k_copy_nodes<T>), dim3(blocks(n), ncol), dim3(256), 0, s, nodes, n, src, dst, ld);
   return hipGetLastError();
 }
 
-hipError_t launch_cut_solve_mfma(int d, int k, const KLevel& L, const CutGroupDev& G, const float* x, const float* b,
-                                 float* W, float* dbuf, int ncol, hipStream_t s) {
+template <typename T>
+hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const T* x, const T* b, T* dbuf,
+                           int ncol, hipStream_t s, T* xb, const CopyJob& cj, const LaunchPolicy& lp) {
   if (G.n_patch == 0) return hipSuccess;
-  if (!G.inv_tiles || !G.tile_off || ncol < 1 || ncol > kMaxCols) return hipErrorInvalidValue;
+  if (ncol < 1 || ncol > kMaxCols || (xb == nullptr && cj.n != 0)) return hipErrorInvalidValue;
+  if (std::is_same<T, float>::value && (!G.inv_tiles || !G.tile_off)) return hipErrorInvalidValue;
   return dispatch(d, k, [&](auto D, auto K) {
-    if (L.n_faces > 0 || t_rec) {  // ghost-face jumps of the current x, all columns
-      const dim3 g(std::max(1u, blocks(L.n_faces)), ncol);
-      if (!record<256>(g, dim3(256), dev::FaceWArgs<D.value, K.value, float>{L, x, W})) {
-        hipLaunchKernelGGL((dev::k_face_w<D.value, K.value, float>), g, dim3(256), 0, s, L, x, W);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
+    auto go = [&](auto nw) {
+      constexpr int NW = decltype(nw)::value;
+      using C = dev::ColsShape<D.value, K.value, T, NW>;
+      CopyJob c2 = cj;
+      c2.nblk = static_cast<int>((cj.n + C::TH * C::COPY - 1) / (C::TH * C::COPY));
+      const dim3 g(c2.nblk + G.n_patch);
+      if (record<C::TH>(g, dim3(C::TH), dev::CutColsArgs<D.value, K.value, T, NW>{L, G, x, b, dbuf, xb, c2, ncol}))
+        return hipSuccess;
+      hipLaunchKernelGGL((dev::k_cut_cols<D.value, K.value, T, NW>), g, dim3(C::TH), 0, s, L, G, x, b, dbuf, xb, c2,
+                         ncol);
+      return hipGetLastError();
+    };
+    // Q1 patches have one internal node.  Else 4 waves (one per cell in 2-D,
+    // two cells each in 3-D); in 3-D launches that leave CUs idle take 8, which
+    // shortens a patch's serial chain (Q2 in FP64, 5 columns, 13..24 patches:
+    // 14.4 -> 11.2 us; at 3,372 Q3 patches 8 waves cost 8%).  Grouped launches
+    // must not depend on a member's patch count and carry several members'
+    // patches: 4 waves (8 cost 27% on eight Q2 problems at 32^3 cells).  The
+    // arithmetic is the same.
+    if constexpr (K.value == 1) {
+      return go(std::integral_constant<int, 1>{});
+    } else {
+      if (D.value == 3 && !t_rec && 3 * (int64_t)G.n_patch < lp.small_cut_launch)
+        return go(std::integral_constant<int, D.value == 3 ? 8 : 4>{});
+      return go(std::integral_constant<int, 4>{});
     }
-    constexpr int TH = dev::CutShape<D.value, K.value>::THREADS;
-    if (record<TH>(dim3(G.n_patch), dim3(TH), dev::CutSolveMfmaArgs<D.value, K.value>{L, G, x, b, W, dbuf, ncol}))
-      return hipSuccess;
-    hipLaunchKernelGGL((dev::k_cut_solve_mfma<D.value, K.value>), dim3(G.n_patch), dim3(TH), 0, s, L, G, x, b, W,
-                       dbuf, ncol);
-    return hipGetLastError();
-  });
-}
-
-hipError_t launch_cut_solve_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const double* x,
-                                 const double* b, double* W, double* dbuf, int ncol, hipStream_t s) {
-  if (G.n_patch == 0) return hipSuccess;
-  if (ncol < 1 || ncol > kMaxCols) return hipErrorInvalidValue;
-  return dispatch(d, k, [&](auto D, auto K) {
-    if (L.n_faces > 0 || t_rec) {  // ghost-face jumps of the current x, all columns
-      const dim3 g(std::max(1u, blocks(L.n_faces)), ncol);
-      if (!record<256>(g, dim3(256), dev::FaceWArgs<D.value, K.value, double>{L, x, W})) {
-        hipLaunchKernelGGL((dev::k_face_w<D.value, K.value, double>), g, dim3(256), 0, s, L, x, W);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
-    }
-    constexpr int TH = dev::CutShape<D.value, K.value>::THREADS;
-    if (record<TH>(dim3(G.n_patch), dim3(TH), dev::CutSolveColsArgs<D.value, K.value>{L, G, x, b, W, dbuf, ncol}))
-      return hipSuccess;
-    hipLaunchKernelGGL((dev::k_cut_solve_cols<D.value, K.value>), dim3(G.n_patch), dim3(TH), 0, s, L, G, x, b, W,
-                       dbuf, ncol);
-    return hipGetLastError();
   });
 }
 
@@ -2522,6 +2691,8 @@ hipError_t launch_gather(const int32_t* dof_node, int64_t n, const TS* lat, TD* 
                                               hipStream_t, int, const LaunchPolicy&);                              \
   template hipError_t launch_cut_solve<T>(int, int, const KLevel&, const CutGroupDev&, const T*, const T*, T*,    \
                                           hipStream_t, int, T*, const CopyJob&, const LaunchPolicy&);              \
+  template hipError_t launch_cut_cols<T>(int, int, const KLevel&, const CutGroupDev&, const T*, const T*, T*, int, \
+                                         hipStream_t, T*, const CopyJob&, const LaunchPolicy&);                     \
   template hipError_t launch_copy_nodes<T>(const int32_t*, int64_t, const T*, T*, int64_t, hipStream_t, int);      \
   template hipError_t launch_cut_update<T>(const CutGroupDev&, const T*, T*, int64_t, hipStream_t, int);          \
   template hipError_t launch_prolong_add<T>(int, int, const KLevel&, const KLevel&, const T*, T*, hipStream_t,     \
