@@ -564,6 +564,29 @@ __device__ __forceinline__ double tile1d_rt(const double* e, int s, int j) {
   return v;
 }
 
+// A run-time row s >= K of the assembled 1-D matrices of a tile: 2k+1 taps from
+// column first on, the last k of them step apart.  A cell boundary couples
+// with both its cells (step 1); any other node, and the line's last one, only
+// with the k+1 nodes of one cell: its further taps repeat that cell's last
+// node with zero entries, so no node outside its cells is ever read.
+template <int K, int NCELL, typename T>
+struct TileRow {
+  int first, step;
+  T m[2 * K + 1], k[2 * K + 1];
+  __device__ __forceinline__ void load(const double* em, const double* ek, int s) {
+    const bool wide = s % K == 0 && s < NCELL * K;
+    first = wide ? s - K : s == NCELL * K ? s - K : K * (s / K);
+    step = wide ? 1 : 0;
+#pragma unroll
+    for (int t = 0; t <= 2 * K; ++t) {
+      const bool has = wide || t <= K;
+      m[t] = has ? (T)tile1d_rt<K, NCELL>(em, s, first + t) : (T)0;
+      k[t] = has ? (T)tile1d_rt<K, NCELL>(ek, s, first + t) : (T)0;
+    }
+  }
+  __device__ __forceinline__ int at(int t) const { return first + (t <= K ? t : K + (t - K) * step); }
+};
+
 // y = A x (b == nullptr) or y = b - A x on the active nodes of a tile whose
 // staged cells -1 .. B-1 are all active and regular.  There A is the sum over
 // directions a of tensor products of the assembled 1-D stiffness h^(d-2) K1
@@ -573,49 +596,123 @@ __device__ __forceinline__ double tile1d_rt(const double* e, int s, int j) {
 // and Khat x on the owned rows; in 3-D the next direction gives Mhat Mhat x and
 // Khat Mhat x + Mhat Khat x; every owned node contracts direction 0 at its own
 // position.  Only the band of the 1-D matrices is applied.
-template <int D, int K, typename T>
-__device__ __forceinline__ void apply_sf_body(KLevel L, const T* __restrict__ x, const T* __restrict__ b,
-                                              T* __restrict__ y) {
-  using S = Shape<D, K>;
-  using A = ApplyShape<D, K>;
-  constexpr int N1 = S::N1, B = A::B, R1 = A::R1, C1 = A::C1, O1 = A::O1;
-  constexpr int NW = D == 3 ? R1 * O1 * O1 : 1;                      // values per second-pass array
-  constexpr int NXV = D == 3 ? (A::NR > 2 * NW ? A::NR : 2 * NW) : A::NR;
-  constexpr int NU = D == 3 ? R1 * R1 * O1 : R1 * O1;                // values per first-pass array
-  __shared__ double m1[N1 * N1], k1[N1 * N1];
-  __shared__ T xv[NXV];     // x staged; in 3-D then the second pass: [0, NW) and [NW, 2 NW)
-  __shared__ T ua[2][NU];   // first pass: Mhat x and Khat x along the slowest direction
-  for (int i = threadIdx.x; i < N1 * N1; i += blockDim.x) {
-    m1[i] = L.tables[S::T_MHAT + i];
-    k1[i] = L.tables[S::T_K1S + i];
-  }
+//
+// 2-D: a thread keeps one (line, row) of the first pass and one owned node of
+// the second for all tiles of its block, so the entries of both rows stay in
+// its registers; a block works on as many tiles at once as its threads cover,
+// and the next tiles' x is on its way while the current ones are contracted.
+// The former form gave the first pass one thread per line, 16 of 256 for Q3.
+// Circle, Q3, 1024^2 cells (6.1 million DoFs), FP64: 298 -> 95 us; now bound by
+// the 22 LDS reads of a node (one 8-byte word a clock and bank pair).
+template <int K, typename T>
+__device__ __forceinline__ void apply_sf2_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                               T* __restrict__ y) {
+  using S = Shape<2, K>;
+  using A = ApplyShape<2, K>;
+  constexpr int B = A::B, R1 = A::R1, C1 = A::C1, O1 = A::O1, NR = R1 * R1, TP = 256 / NR;
+  static_assert(TP >= 1, "a thread per staged node");
+  __shared__ T xv[TP][NR];
+  __shared__ T um[TP][O1 * R1], uk[TP][O1 * R1];
   x += blockIdx.y * L.n_nodes;  // column blockIdx.y
   if (b) b += blockIdx.y * L.n_nodes;
   y += blockIdx.y * L.n_nodes;
   const int NTd = (L.N + B - 1) / B;
+  const int p = threadIdx.x / NR, r = threadIdx.x % NR;
+  const int i0 = r % R1, i1 = r / R1;  // staged node, and (line, row) of the first pass
+  const int q0 = r % O1, q1 = r / O1;  // owned node
+  TileRow<K, C1, T> r1, r0;
+  r1.load(L.tables + S::T_MHAT, L.tables + S::T_K1S, K + (i1 < O1 ? i1 : 0));
+  r0.load(L.tables + S::T_MHAT, L.tables + S::T_K1S, K + q0);
+  const int step = gridDim.x * TP;
+  auto load = [&](int ti, int& tile) {
+    tile = p < TP && ti < L.n_tiles_sf ? L.tiles_sf[ti] : -1;
+    if (tile < 0) return (T)0;
+    return x[K * (B * (tile % NTd) - 1) + i0 + (int64_t)L.nn * (K * (B * (tile / NTd) - 1) + i1)];
+  };
+  int tile;
+  T v = load(blockIdx.x * TP + p, tile);
+  for (int t0 = blockIdx.x * TP; t0 < L.n_tiles_sf; t0 += step) {
+    const int tc = tile;
+    if (p < TP) xv[p][r] = v;
+    __syncthreads();  // x staged, and the previous tiles' second pass is done
+    v = load(t0 + step + p, tile);
+    if (tc >= 0 && i1 < O1) {
+      T am = 0, ak = 0;
+#pragma unroll
+      for (int t = 0; t <= 2 * K; ++t) {
+        const T xt = xv[p][i0 + R1 * r1.at(t)];
+        am += r1.m[t] * xt;
+        ak += r1.k[t] * xt;
+      }
+      um[p][i0 + R1 * i1] = am;
+      uk[p][i0 + R1 * i1] = ak;
+    }
+    __syncthreads();
+    if (tc >= 0 && q1 < O1) {
+      const int c0 = tc % NTd, c1 = tc / NTd;
+      // the layer q = B K belongs to the next tile unless this is the last one
+      if ((q0 < B * K || c0 == NTd - 1) && (q1 < B * K || c1 == NTd - 1)) {
+        const int64_t node = K * B * c0 + q0 + (int64_t)L.nn * (K * B * c1 + q1);
+        const T bv = b ? b[node] : (T)0;
+        T ax = 0;
+#pragma unroll
+        for (int t = 0; t <= 2 * K; ++t) {
+          const int at = r0.at(t) + R1 * q1;
+          ax += r0.k[t] * um[p][at];
+          ax += r0.m[t] * uk[p][at];
+        }
+        y[node] = b ? bv - ax : ax;
+      }
+    }
+  }
+}
+
+// 3-D: the entries of the first two passes are read at compile-time places of
+// the level tables (scalar registers), those of the last from a table of the
+// owned rows in LDS, where they were summed again at every use.  Finest
+// level of the 128^3 ball, Q2, FP64: 63.6 -> 48.6 us.
+template <int K, typename T>
+__device__ __forceinline__ void apply_sf3_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                               T* __restrict__ y) {
+  using S = Shape<3, K>;
+  using A = ApplyShape<3, K>;
+  constexpr int B = A::B, R1 = A::R1, C1 = A::C1, O1 = A::O1;
+  constexpr int NW = R1 * O1 * O1;                       // values per second-pass array
+  constexpr int NXV = A::NR > 2 * NW ? A::NR : 2 * NW;
+  constexpr int NU = R1 * R1 * O1;                       // values per first-pass array
+  __shared__ T xv[NXV];     // x staged, then the second pass: [0, NW) and [NW, 2 NW)
+  __shared__ T ua[2][NU];   // first pass: Mhat x and Khat x along the slowest direction
+  __shared__ TileRow<K, C1, T> rows[O1];
+  const double* m1 = L.tables + S::T_MHAT;
+  const double* k1 = L.tables + S::T_K1S;
+  if (threadIdx.x < O1) rows[threadIdx.x].load(m1, k1, K + threadIdx.x);
+  x += blockIdx.y * L.n_nodes;  // column blockIdx.y
+  if (b) b += blockIdx.y * L.n_nodes;
+  y += blockIdx.y * L.n_nodes;
+  const int NTd = (L.N + B - 1) / B;
+  const int64_t nn = L.nn;
   for (int ti = blockIdx.x; ti < L.n_tiles_sf; ti += gridDim.x) {
     __syncthreads();  // tables, and the previous tile finished with the LDS buffers
-    int tc[3] = {0, 0, 0};
+    const int tile = L.tiles_sf[ti];
+    const int tc[3] = {tile % NTd, (tile / NTd) % NTd, tile / (NTd * NTd)};
+    const T* xt = x + K * (B * tc[0] - 1) + nn * (K * (B * tc[1] - 1) + nn * (K * (B * tc[2] - 1)));
     {
-      int r = L.tiles_sf[ti];
+      constexpr int NIT = (A::NR + 255) / 256;
+      T v[NIT];
 #pragma unroll
-      for (int a = 0; a < D; ++a) { tc[a] = r % NTd; r /= NTd; }
-    }
-    for (int e = threadIdx.x; e < A::NR; e += blockDim.x) {
-      int I[3];
-      bool in = true;
-      int r = e;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        I[a] = K * (B * tc[a] - 1) + r % R1;
-        r /= R1;
-        in = in && I[a] >= 0 && I[a] < L.nn;
+      for (int u = 0; u < NIT; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        v[u] = e < A::NR ? xt[e % R1 + nn * ((e / R1) % R1 + nn * (e / (R1 * R1)))] : (T)0;
       }
-      xv[e] = in ? x[lat(D, L.nn, I)] : (T)0;
+#pragma unroll
+      for (int u = 0; u < NIT; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        if (e < A::NR) xv[e] = v[u];
+      }
     }
     __syncthreads();
     // slowest direction: every staged line, rows K .. K + O1 - 1
-    constexpr int NLA = D == 3 ? R1 * R1 : R1;
+    constexpr int NLA = R1 * R1;
     for (int l = threadIdx.x; l < NLA; l += blockDim.x) {
       T xl[R1];
 #pragma unroll
@@ -634,70 +731,62 @@ __device__ __forceinline__ void apply_sf_body(KLevel L, const T* __restrict__ x,
       }
     }
     __syncthreads();
-    if constexpr (D == 3) {
-      // direction 1 on the lines (s0, q2): Mhat Mhat x into [0, NW), Khat Mhat x + Mhat Khat x into [NW, 2 NW)
-      for (int t = threadIdx.x; t < R1 * O1; t += blockDim.x) {
-        const int s0 = t % R1, q2 = t / R1;
-        T ul[R1], kl[R1];
+    // direction 1 on the lines (s0, q2): Mhat Mhat x into [0, NW), Khat Mhat x + Mhat Khat x into [NW, 2 NW)
+    for (int t = threadIdx.x; t < R1 * O1; t += blockDim.x) {
+      const int s0 = t % R1, q2 = t / R1;
+      T ul[R1], kl[R1];
+#pragma unroll
+      for (int j = 0; j < R1; ++j) {
+        ul[j] = ua[0][(s0 + R1 * j) * O1 + q2];
+        kl[j] = ua[1][(s0 + R1 * j) * O1 + q2];
+      }
+#pragma unroll
+      for (int q = 0; q < O1; ++q) {
+        T vmm = 0, vxx = 0;
 #pragma unroll
         for (int j = 0; j < R1; ++j) {
-          ul[j] = ua[0][(s0 + R1 * j) * O1 + q2];
-          kl[j] = ua[1][(s0 + R1 * j) * O1 + q2];
+          if (!tile1d_nz<K, C1>(K + q, j)) continue;
+          vmm += (T)tile1d<K, C1>(m1, K + q, j) * ul[j];
+          vxx += (T)tile1d<K, C1>(k1, K + q, j) * ul[j];
+          vxx += (T)tile1d<K, C1>(m1, K + q, j) * kl[j];
         }
-#pragma unroll
-        for (int q = 0; q < O1; ++q) {
-          T vmm = 0, vxx = 0;
-#pragma unroll
-          for (int j = 0; j < R1; ++j) {
-            if (!tile1d_nz<K, C1>(K + q, j)) continue;
-            vmm += (T)tile1d<K, C1>(m1, K + q, j) * ul[j];
-            vxx += (T)tile1d<K, C1>(k1, K + q, j) * ul[j];
-            vxx += (T)tile1d<K, C1>(m1, K + q, j) * kl[j];
-          }
-          xv[s0 + R1 * (q + O1 * q2)] = vmm;
-          xv[NW + s0 + R1 * (q + O1 * q2)] = vxx;
-        }
+        xv[s0 + R1 * (q + O1 * q2)] = vmm;
+        xv[NW + s0 + R1 * (q + O1 * q2)] = vxx;
       }
-      __syncthreads();
     }
+    __syncthreads();
     // direction 0 at every owned node: Khat (first array) + Mhat (second array)
-    const T* f0 = D == 3 ? xv : &ua[0][0];
-    const T* f1 = D == 3 ? xv + NW : &ua[1][0];
 #pragma unroll 1
     for (int e = threadIdx.x; e < A::NO; e += blockDim.x) {
-      int q[3], I[3];
+      const int q[3] = {e % O1, (e / O1) % O1, e / (O1 * O1)};
       bool own = true;
-      int r = e;
+      // the layer q = B K belongs to the next tile unless this is the last one
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        q[a] = r % O1;
-        r /= O1;
-        I[a] = K * B * tc[a] + q[a];
-        // the layer q = B K belongs to the next tile unless this is the last one
-        own = own && I[a] < L.nn && (q[a] < B * K || tc[a] == NTd - 1);
-      }
+      for (int a = 0; a < 3; ++a) own = own && (q[a] < B * K || tc[a] == NTd - 1);
       if (!own) continue;
-      const int64_t node = lat(D, L.nn, I);
+      const int64_t node = K * B * tc[0] + q[0] + nn * (K * B * tc[1] + q[1] + nn * (K * B * tc[2] + q[2]));
       const T bv = b ? b[node] : (T)0;
-      const int s = K + q[0];
-      // second-pass value of staged column j: 3-D index j + R1 (q1 + O1 q2), 2-D j O1 + q1
-      const int rest = D == 3 ? R1 * (q[1] + O1 * q[2]) : q[1];
+      const TileRow<K, C1, T>& rw = rows[q[0]];
+      const int rest = R1 * (q[1] + O1 * q[2]);
       T ax = 0;
 #pragma unroll
-      for (int dj = -K; dj <= K; ++dj) {
-        // s >= K, so j >= 0; the line ends at R1 - 1 = (B + 1) K, so for K >= 2
-        // the last owned rows reach past it: those j hold no matrix entry, and
-        // the words past the line were not written by this block (not
-        // necessarily finite), so they are skipped
-        const int j = s + dj;
-        if (j >= R1) continue;
-        const int at = D == 3 ? j + rest : j * O1 + rest;
-        ax += (T)tile1d_rt<K, C1>(k1, s, j) * f0[at];
-        ax += (T)tile1d_rt<K, C1>(m1, s, j) * f1[at];
+      for (int t = 0; t <= 2 * K; ++t) {
+        const int at = rw.at(t) + rest;
+        ax += rw.k[t] * xv[at];
+        ax += rw.m[t] * xv[NW + at];
       }
       y[node] = b ? bv - ax : ax;
     }
   }
+}
+
+template <int D, int K, typename T>
+__device__ __forceinline__ void apply_sf_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                              T* __restrict__ y) {
+  if constexpr (D == 2)
+    apply_sf2_body<K, T>(L, x, b, y);
+  else
+    apply_sf3_body<K, T>(L, x, b, y);
 }
 
 template <int D, int K, typename T>
