@@ -365,7 +365,7 @@ def algorithmic_bytes(P, w, kind: str, s: int = 8, m: int = 1, two_buffer: bool 
         flags = N.reshape((Nc,) * d)  # index order (z, y, x) / (y, x)
         cut = (flags & 2) != 0
         copy = {}
-        if kind == "cut_solve" and two_buffer:  # (the multi-column steps have no copy blocks)
+        if kind == "cut_solve" and two_buffer:
             nodes = {c: P.export(l, 32 + c, np.int32) for c in range(2 ** d)}
             present = [c for c in range(2 ** d) if len(nodes[c])]
             for i, c in enumerate(present):
@@ -405,22 +405,29 @@ def algorithmic_bytes(P, w, kind: str, s: int = 8, m: int = 1, two_buffer: bool 
 def vcycle_bytes(P, w, s: int = 8, m: int = 1, dense: bool = False) -> int:
     """Algorithmic bytes of one whole V-cycle (one pre- and one post-smoothing
     step per level, n_c sweeps over the cut colours):
-        sum_{l >= 1} [2 (S_int + n_c S_cut) + R + T] + s (n_0^2 + 2 n_0)
+        sum_{l > d} [2 (S_int + n_c S_cut) + R + T] + s (n_d^2 + 2 n_d)
     with S_int / S_cut the interior / cut colour steps of a sweep (per patch as
     in algorithmic_bytes, copy blocks of the two-buffer steps included), R the
     level residual b - A x, T the transfers s (3 n_l + 2 n_{l-1}) (prolongation
     reads e and x and writes x, restriction reads r and writes the coarse b),
-    and the coarse solve a GEMV with the dense inverse.  With m columns the
-    matrix terms count once; dense as in algorithmic_bytes."""
+    and a GEMV with the dense V-cycle of the levels 0..d (d: the finest level
+    below the top with at most 2048 DoFs; 0: the dense coarse inverse).  With m
+    columns the matrix terms count once; dense as in algorithmic_bytes."""
+    n = [P.counts(l)["n_dofs"] for l in range(w.n_levels)]
+    d = max([l for l in range(1, w.n_levels - 1) if n[l] <= 2048], default=0)
+
+    def run(per):
+        return {key: v for key, v in per.items() if key == "cg" or (key[0] if isinstance(key, tuple) else key) > d}
+
     inter = algorithmic_bytes(P, w, "interior_step", s, m)
-    cut = algorithmic_bytes(P, w, "cut_solve", s, m, two_buffer=(m == 1))
-    app = algorithmic_bytes(P, w, "apply", s, m, dense=dense)
+    cut = run(algorithmic_bytes(P, w, "cut_solve", s, m))
+    app = run(algorithmic_bytes(P, w, "apply", s, m, dense=dense))
+    inter = run(inter)
     total = 2 * sum(inter.values()) + 2 * w.n_c * sum(cut.values())
     total += sum(v for key, v in app.items() if key != "cg")
-    n = [P.counts(l)["n_dofs"] for l in range(w.n_levels)]
-    for l in range(1, w.n_levels):
+    for l in range(d + 1, w.n_levels):
         total += s * m * (3 * n[l] + 2 * n[l - 1])
-    total += s * n[0] * n[0] + 2 * s * m * n[0]
+    total += s * n[d] * n[d] + 2 * s * m * n[d]
     return int(total)
 
 
@@ -509,7 +516,7 @@ def timed_multi_solves(P, w, B, args, fp32: bool) -> dict:
     dt = time.perf_counter() - t0
     launches, kms = P.timing_read(args.kernel, fine)
     P.timing([])
-    roof = roofline(P, w, args.kernel, launches, kms, vcyc, fp32, ncol=nrhs, two_buffer=False, level=fine)
+    roof = roofline(P, w, args.kernel, launches, kms, vcyc, fp32, ncol=nrhs, level=fine)
     tag = "fp32" if fp32 else "fp64"
     print(f"[bench] {tag} x{nrhs}: timed {args.steps} solves: {dt:.3f}s, {vcyc} multi V-cycles", file=sys.stderr,
           flush=True)

@@ -131,6 +131,9 @@ struct cmg_problem {
   std::vector<void*> owned;
   double* coarse64 = nullptr;
   float* coarse32 = nullptr;
+  int dense_level = 0;        // the V-cycle of levels 0..dense_level as one dense matrix (0: none), see dense_level_of
+  double* dense64 = nullptr;
+  float* dense32 = nullptr;
   bool fp32_ready = false;
   bool fp32 = false;  // precision of the V-cycle
   bool m64_ready = false, m32_ready = false, tiles_ready = false;
@@ -222,6 +225,31 @@ template <>
 double* coarse_inv<double>(cmg_problem* P) { return P->coarse64; }
 template <>
 float* coarse_inv<float>(cmg_problem* P) { return P->coarse32; }
+
+template <typename T>
+T* dense_op(cmg_problem* P);
+template <>
+double* dense_op<double>(cmg_problem* P) { return P->dense64; }
+template <>
+float* dense_op<float>(cmg_problem* P) { return P->dense32; }
+
+// The V-cycle with zero initial guess is linear, so on the smallest levels,
+// where it is a chain of short launches (33 a level in 2-D, 57 in 3-D, 2 to 9
+// us each) rather than work, it is applied as one dense matrix.  The level: the
+// finest one below the top with at most kDenseMax DoFs.  Its product reads 8 n^2
+// bytes (33 MB at the limit, about 10 us) in place of the chain of its levels:
+// V-cycle 382 -> 159 us (disc, Q2, 32^2: levels 1 and 2), 1341 -> 939 us (circle,
+// Q2, 512^2: 1 to 3), 1228 -> 902 us (ball, Q2, 32^3: 1).  Making it costs the
+// set-up n columns of the V-cycle it replaces, 1 ms (n = 529) to 9 ms (n = 1,701,
+// 5% of that set-up), which one to three solves give back; at n = 4,096 it would
+// be tens of ms.  0: none (level 0 has its exact inverse anyway).
+constexpr int64_t kDenseMax = 2048;
+int dense_level_of(const cmg::Hierarchy& H) {
+  for (int l = static_cast<int>(H.levels.size()) - 2; l >= 1; --l)
+    if (H.levels[l].n_dofs <= kDenseMax) return l;
+  return 0;
+}
+cmg_status build_dense(cmg_problem* P);
 
 template <typename T>
 cmg_status upload(std::vector<void*>& owned, const T* host, size_t n, T** dptr) {
@@ -446,6 +474,7 @@ cmg_status upload_all(cmg_problem* P) {
   P->nblk = static_cast<int>(std::min<int64_t>(1024, (n + 255) / 256));
   TRY(alloc_zero(own, static_cast<size_t>(P->nblk), &P->part));
   HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&P->part_host), P->nblk * sizeof(double), hipHostMallocDefault));
+  TRY(build_dense(P));
   return settle();
 }
 
@@ -482,6 +511,11 @@ cmg_status ensure_fp32(cmg_problem* P) {
     if (d.n_region > 0) TRY(alloc_zero(own, h.n_nodes, &d.v32.x1));
   }
   TRY(upload_f32(own, P->H.coarse_inv, &P->coarse32));
+  if (P->dense_level > 0) {
+    const int64_t n = P->H.levels[P->dense_level].n_dofs;
+    TRY(alloc_zero(own, static_cast<size_t>(n * n), &P->dense32));
+    HIP_TRY(cmg::launch_round(n * n, P->dense64, P->dense32, nullptr));
+  }
   TRY(settle());
   P->fp32_ready = true;
   return CMG_OK;
@@ -756,12 +790,15 @@ cmg_status smooth(cmg_problem* P, int l, bool post, hipStream_t s, int ncol = 1,
   return CMG_OK;
 }
 
+// x_l = M b_l with the exact coarse inverse (l = 0) or the dense V-cycle of the
+// levels 0..l.
 template <typename T>
-cmg_status coarse(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false) {
-  DevLevel& D = P->lv[0];
-  KTimer t(P, kCoarse, 0, s);
-  HIP_TRY(cmg::launch_coarse<T>(coarse_inv<T>(P), D.kl64.dof_node, static_cast<int>(P->H.n_coarse),
-                                work<T>(D, multi).b, work<T>(D, multi).x, D.kl64.n_nodes, s, ncol));
+cmg_status coarse(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false, int l = 0) {
+  DevLevel& D = P->lv[l];
+  KTimer t(P, kCoarse, l, s);
+  HIP_TRY(cmg::launch_coarse<T>(l > 0 ? dense_op<T>(P) : coarse_inv<T>(P), D.kl64.dof_node,
+                                static_cast<int>(P->H.levels[l].n_dofs), work<T>(D, multi).b, work<T>(D, multi).x,
+                                D.kl64.n_nodes, s, ncol));
   return CMG_OK;
 }
 
@@ -798,23 +835,75 @@ cmg_status restrict_(cmg_problem* P, int l, const T* rf, hipStream_t s, int ncol
   return CMG_OK;
 }
 
-// V-cycle on the lattice vectors of precision T: x_L = B b_L, zero initial guess.
+// V-cycle of the levels bottom..top on the lattice vectors of precision T:
+// x_top = B b_top, zero initial guess; level `bottom` is solved by its dense
+// matrix (coarse).
 template <typename T>
-cmg_status vcycle_lattice(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false) {
-  const int L = P->H.cfg.n_levels - 1;
-  for (int l = L; l >= 1; --l) {
+cmg_status vcycle_levels(cmg_problem* P, int bottom, int top, hipStream_t s, int ncol, bool multi) {
+  for (int l = top; l > bottom; --l) {
     Vecs<T>& v = work<T>(P->lv[l], multi);
     TRY(zero_active<T>(P, l, v.x, s, ncol));
     TRY(smooth<T>(P, l, false, s, ncol, multi));
     TRY(apply_lat<T>(P, l, v.x, v.b, v.r, s, ncol, multi));
     TRY(restrict_<T>(P, l, v.r, s, ncol, multi));
   }
-  TRY(coarse<T>(P, s, ncol, multi));
-  for (int l = 1; l <= L; ++l) {
+  TRY(coarse<T>(P, s, ncol, multi, bottom));
+  for (int l = bottom + 1; l <= top; ++l) {
     TRY(prolong_add<T>(P, l, s, ncol, multi));
     TRY(smooth<T>(P, l, true, s, ncol, multi));
   }
   return CMG_OK;
+}
+
+// The whole V-cycle.  The dense matrix of the smallest levels belongs to the
+// exact ghost coupling; with the patch-local one every level is run.
+template <typename T>
+cmg_status vcycle_lattice(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false) {
+  return vcycle_levels<T>(P, P->ghost_local ? 0 : P->dense_level, P->H.cfg.n_levels - 1, s, ncol, multi);
+}
+
+// The dense V-cycle of the levels 0..dense_level: the FP64 V-cycle of those
+// levels applied to the unit vectors, a batch of columns per launch sequence, on
+// work vectors that are released again.  Part of the set-up (null stream).
+cmg_status build_dense(cmg_problem* P) {
+  const int l0 = dense_level_of(P->H);
+  if (l0 == 0) return CMG_OK;
+  const int64_t n = P->H.levels[l0].n_dofs;
+  TRY(alloc_zero(P->owned, static_cast<size_t>(n * n), &P->dense64));
+  // about 128 MB of work vectors at a time
+  size_t per = 0;
+  for (int l = 0; l <= l0; ++l) {
+    const DevLevel& d = P->lv[l];
+    per += 8 * (4 * static_cast<size_t>(d.kl64.n_nodes) + d.n_w + d.n_c + static_cast<size_t>(d.max_cut_nodes));
+  }
+  const int64_t batch = std::min<int64_t>(n, std::max<int64_t>(cmg::kMaxCols, (int64_t{128} << 20) / static_cast<int64_t>(per)));
+  const size_t C = static_cast<size_t>(batch);
+  std::vector<void*> tmp;
+  auto run = [&]() -> cmg_status {
+    for (int l = 0; l <= l0; ++l) {
+      DevLevel& d = P->lv[l];
+      const size_t nn = static_cast<size_t>(d.kl64.n_nodes);
+      for (double** v : {&d.m64.x, &d.m64.b, &d.m64.r, &d.m64.x1}) TRY(alloc_zero(tmp, C * nn, v));
+      TRY(alloc_zero(tmp, C * d.n_w, &d.m64.W));
+      TRY(alloc_zero(tmp, C * d.n_c, &d.m64.C));
+      TRY(alloc_zero(tmp, C * static_cast<size_t>(d.max_cut_nodes), &d.m64.dbuf));
+      if (d.n_region == 0) d.m64.x1 = nullptr;
+    }
+    DevLevel& D = P->lv[l0];
+    for (int64_t c0 = 0; c0 < n; c0 += batch) {
+      const int nc = static_cast<int>(std::min(batch, n - c0));
+      HIP_TRY(cmg::launch_units(D.kl64.dof_node, n, c0, nc, D.m64.b, D.kl64.n_nodes, nullptr));
+      TRY(vcycle_levels<double>(P, 0, l0, nullptr, nc, true));
+      HIP_TRY(cmg::launch_put_columns(D.kl64.dof_node, n, c0, nc, D.m64.x, D.kl64.n_nodes, P->dense64, nullptr));
+    }
+    return settle();
+  };
+  const cmg_status st = run();
+  if (st != CMG_OK) (void)hipStreamSynchronize(nullptr);
+  for (int l = 0; l <= l0; ++l) P->lv[l].m64 = Vecs<double>();
+  for (void* v : tmp) (void)hipFree(v);
+  if (st == CMG_OK) P->dense_level = l0;
+  return st;
 }
 
 template <typename T>
@@ -1185,8 +1274,10 @@ size_t hierarchy_bytes(const cmg::Hierarchy& H, int flags) {
   }
   const size_t nL = static_cast<size_t>(H.levels.back().n_dofs);
   const size_t n0sq = static_cast<size_t>(H.n_coarse) * static_cast<size_t>(H.n_coarse);
-  b64 += 8 * n0sq + 8 * 4 * nL + 8 * 1024;
-  b32 += 4 * n0sq;
+  const int ld = dense_level_of(H);
+  const size_t nd = ld > 0 ? static_cast<size_t>(H.levels[ld].n_dofs) : 0;
+  b64 += 8 * (n0sq + nd * nd) + 8 * 4 * nL + 8 * 1024;
+  b32 += 4 * (n0sq + nd * nd);
   m64 += 8 * 4 * C * nL + 8 * C * 1024;
   return b64 + (fp32 ? b32 : 0) + (multi ? m64 + (fp32 ? m32 : 0) : 0);
 }

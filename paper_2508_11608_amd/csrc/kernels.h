@@ -154,8 +154,8 @@ CopyJob cut_copy_job(int d, int k, const CutGroupDev& Gp, int mask);
 template <typename T>
 hipError_t launch_copy_nodes(const int32_t* nodes, int64_t n, const T* src, T* dst, int64_t ld, hipStream_t s,
                              int ncol = 1);
-// The cut colour step of 1 <= ncol <= kMaxCols columns, one patch block for all
-// of them, on the matrix cores (FP32 needs inv_tiles); xb and cj as in
+// The cut colour step of several columns, one patch block for every kMaxCols of
+// them, on the matrix cores (FP32 needs inv_tiles); xb and cj as in
 // launch_cut_solve.
 template <typename T>
 hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const T* x, const T* b, T* dbuf,
@@ -169,9 +169,17 @@ hipError_t launch_prolong_add(int d, int k, const KLevel& Lc, const KLevel& Lf, 
 template <typename T>
 hipError_t launch_restrict(int d, int k, const KLevel& Lc, const KLevel& Lf, const T* rf, T* bc, hipStream_t s,
                            int ncol = 1);
+// x = M b on the active nodes of one level, M a dense n x n matrix
 template <typename T>
-hipError_t launch_coarse(const T* inv, const int32_t* dof_node, int n0, const T* b, T* x, int64_t ld, hipStream_t s,
+hipError_t launch_coarse(const T* inv, const int32_t* dof_node, int n, const T* b, T* x, int64_t ld, hipStream_t s,
                          int ncol = 1);
+// columns c0 .. c0 + ncol - 1 of the identity on the active nodes of a level (lattice vectors, ld apart);
+// the same columns of a dense n x n matrix from lattice vectors; rounding to FP32
+hipError_t launch_units(const int32_t* dof_node, int64_t n, int64_t c0, int ncol, double* b, int64_t ld,
+                        hipStream_t s);
+hipError_t launch_put_columns(const int32_t* dof_node, int64_t n, int64_t c0, int ncol, const double* x, int64_t ld,
+                              double* m, hipStream_t s);
+hipError_t launch_round(int64_t n, const double* x, float* y, hipStream_t s);
 template <typename T>
 hipError_t launch_zero_active(const int32_t* dof_node, int64_t n, T* x, int64_t ld, hipStream_t s, int ncol = 1);
 template <typename TS, typename TD>

@@ -238,6 +238,11 @@ __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, 
   constexpr int N1 = S::N1, NL = S::NL, CPB = CellShape<D, K>::CPB, NF = 2 * D;
   constexpr int NT = Pow<N1, D - 1>::v;
   constexpr int NPK = NL * (NL + 1) / 2;  // entries of a packed symmetric cell matrix
+  // column group blockIdx.y of at most NCOL columns
+  x += (int64_t)blockIdx.y * NCOL * L.n_nodes;
+  W += (int64_t)blockIdx.y * NCOL * L.n_faces * K * NT;
+  C += (int64_t)blockIdx.y * NCOL * L.n_spec * NL;
+  ncol = ncol - (int)blockIdx.y * NCOL < NCOL ? ncol - (int)blockIdx.y * NCOL : NCOL;
   __shared__ T xs[CPB][NL][NCOL];
   __shared__ T epk[CPB][NPK];
   const int lc = threadIdx.x / NL;
@@ -1767,6 +1772,12 @@ template <int D, int K, typename T, int NW>
 __device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev& G, const T* __restrict__ x,
                                               const T* __restrict__ b, T* __restrict__ dbuf, T* __restrict__ xb,
                                               const CopyJob& cj, int ncol) {
+  // column group blockIdx.y of at most kMaxCols columns
+  x += (int64_t)blockIdx.y * kMaxCols * L.n_nodes;
+  b += (int64_t)blockIdx.y * kMaxCols * L.n_nodes;
+  if (xb) xb += (int64_t)blockIdx.y * kMaxCols * L.n_nodes;
+  if (dbuf) dbuf += (int64_t)blockIdx.y * kMaxCols * G.n_nodes;
+  ncol = ncol - (int)blockIdx.y * kMaxCols < kMaxCols ? ncol - (int)blockIdx.y * kMaxCols : kMaxCols;
   using S = Shape<D, K>;
   using C = ColsShape<D, K, T, NW>;
   using Acc = typename Mfma<T>::Acc;
@@ -2426,39 +2437,99 @@ struct RestrictArgs {
   __device__ void run() const { restrict_body<D, K, T>(Lc, Lf, rf, bc); }
 };
 
-// x_0 = A_0^{-1} b_0 on the coarsest level: one 64-wide wavefront per row.
-template <typename T>
-__device__ __forceinline__ void coarse_body(const T* __restrict__ inv, const int32_t* __restrict__ dof_node, int n0,
-                                            const T* __restrict__ b, T* __restrict__ x, int64_t ld) {
+// x = M b on one level, M dense n x n (row-major): the exact coarse solve, or
+// the dense V-cycle of the smallest levels.  One wavefront per row, the active
+// entries of up to NCOL columns of b staged in LDS run by run, so that a matrix
+// entry is read once for all of them; lane l sums the columns l, l + 64, ... of M
+// in increasing order whatever NCOL is.  Bound by the reads of M once n is
+// large (1,701 rows, FP64, 23 MB: 11 us).
+template <typename T, int NCOL>
+__device__ __forceinline__ void coarse_body(const T* __restrict__ inv, const int32_t* __restrict__ dof_node, int n,
+                                            const T* __restrict__ b, T* __restrict__ x, int64_t ld, int ncol) {
+  constexpr int RUN = NCOL == 1 ? 2048 : 512;
+  __shared__ T bs[NCOL][RUN];
   const int row = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
   const int lane = threadIdx.x % 64;
-  if (row >= n0) return;
-  b += blockIdx.y * ld;  // column blockIdx.y
-  x += blockIdx.y * ld;
-  T s = 0;
-  for (int j = lane; j < n0; j += 64) s += inv[(int64_t)row * n0 + j] * b[dof_node[j]];
+  const int c0 = blockIdx.y * NCOL;  // column group
+  b += c0 * ld;
+  x += c0 * ld;
+  ncol = ncol - c0 < NCOL ? ncol - c0 : NCOL;
+  const T* m = inv + (int64_t)(row < n ? row : 0) * n;
+  T s[NCOL];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (lane == 0) x[dof_node[row]] = s;
+  for (int c = 0; c < NCOL; ++c) s[c] = 0;
+  for (int j0 = 0; j0 < n; j0 += RUN) {
+    const int nr = n - j0 < RUN ? n - j0 : RUN;
+    if (j0 > 0) __syncthreads();
+    for (int j = threadIdx.x; j < nr; j += blockDim.x) {
+      const int64_t nd = dof_node[j0 + j];
+#pragma unroll
+      for (int c = 0; c < NCOL; ++c) bs[c][j] = c < ncol ? b[c * ld + nd] : (T)0;
+    }
+    __syncthreads();
+    if (row < n) {
+#pragma unroll 8
+      for (int j = lane; j < nr; j += 64) {
+        const T e = m[j0 + j];
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) s[c] += e * bs[c][j];
+      }
+    }
+  }
+  if (row >= n) return;
+#pragma unroll
+  for (int c = 0; c < NCOL; ++c)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s[c] += __shfl_down(s[c], o, 64);
+  if (lane == 0) {
+    const int64_t nd = dof_node[row];
+#pragma unroll
+    for (int c = 0; c < NCOL; ++c)
+      if (c < ncol) x[c * ld + nd] = s[c];
+  }
 }
 
-template <typename T>
+template <typename T, int NCOL>
 __global__ __launch_bounds__(256) void k_coarse(const T* __restrict__ inv, const int32_t* __restrict__ dof_node,
-                                                int n0, const T* __restrict__ b, T* __restrict__ x, int64_t ld) {
-  coarse_body<T>(inv, dof_node, n0, b, x, ld);
+                                                int n, const T* __restrict__ b, T* __restrict__ x, int64_t ld,
+                                                int ncol) {
+  coarse_body<T, NCOL>(inv, dof_node, n, b, x, ld, ncol);
 }
 
 // argument record of k_coarse for grouped launches (k_grouped)
-template <typename T>
+template <typename T, int NCOL>
 struct CoarseArgs {
   const T* inv;
   const int32_t* dof_node;
-  int n0;
+  int n;
   const T* b;
   T* x;
   int64_t ld;
-  __device__ void run() const { coarse_body<T>(inv, dof_node, n0, b, x, ld); }
+  int ncol;
+  __device__ void run() const { coarse_body<T, NCOL>(inv, dof_node, n, b, x, ld, ncol); }
 };
+
+// Columns c0 .. c0 + ncol - 1 of the identity on the active nodes of a level.
+__global__ __launch_bounds__(256) void k_units(const int32_t* __restrict__ dof_node, int64_t n, int64_t c0,
+                                               double* __restrict__ b, int64_t ld) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < n) b[blockIdx.y * ld + dof_node[i]] = i == c0 + blockIdx.y ? 1.0 : 0.0;
+}
+
+// The columns c0 .. of a dense n x n matrix (row-major) from lattice vectors.
+__global__ __launch_bounds__(256) void k_put_columns(const int32_t* __restrict__ dof_node, int64_t n, int64_t c0,
+                                                     int ncol, const double* __restrict__ x, int64_t ld,
+                                                     double* __restrict__ m) {
+  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (e >= n * ncol) return;
+  const int64_t i = e / ncol, c = e % ncol;
+  m[i * n + c0 + c] = x[c * ld + dof_node[i]];
+}
+
+__global__ __launch_bounds__(256) void k_round(int64_t n, const double* __restrict__ x, float* __restrict__ y) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < n) y[i] = static_cast<float>(x[i]);
+}
 
 template <typename T>
 __device__ __forceinline__ void zero_active_body(const int32_t* __restrict__ dof_node, int64_t n, T* __restrict__ x,
@@ -2577,7 +2648,8 @@ hipError_t launch_apply(int d, int k, const KLevel& L, const T* x, const T* b, T
     }
     if (L.n_spec > 0 || t_rec) {
       constexpr int CPB = dev::CellShape<D.value, K.value>::CPB;
-      const dim3 g(std::max(1u, static_cast<unsigned>((L.n_spec + CPB - 1) / CPB)));
+      const dim3 g(std::max(1u, static_cast<unsigned>((L.n_spec + CPB - 1) / CPB)),
+                   ncol == 1 ? 1 : (ncol + kMaxCols - 1) / kMaxCols);
       if (ncol == 1) {
         if (!record<64>(g, dim3(64), dev::CellAxArgs<D.value, K.value, T, 1>{L, x, W, C, 1}))
           hipLaunchKernelGGL((dev::k_cell_ax<D.value, K.value, T, 1>), g, dim3(64), 0, s, L, x, W, C, 1);
@@ -2672,7 +2744,7 @@ template <typename T>
 hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, const T* x, const T* b, T* dbuf,
                            int ncol, hipStream_t s, T* xb, const CopyJob& cj, const LaunchPolicy& lp) {
   if (G.n_patch == 0) return hipSuccess;
-  if (ncol < 1 || ncol > kMaxCols || (xb == nullptr && cj.n != 0)) return hipErrorInvalidValue;
+  if (ncol < 1 || (xb == nullptr && cj.n != 0)) return hipErrorInvalidValue;
   if (std::is_same<T, float>::value && (!G.inv_tiles || !G.tile_off)) return hipErrorInvalidValue;
   return dispatch(d, k, [&](auto D, auto K) {
     auto go = [&](auto nw) {
@@ -2680,7 +2752,7 @@ hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, 
       using C = dev::ColsShape<D.value, K.value, T, NW>;
       CopyJob c2 = cj;
       c2.nblk = static_cast<int>((cj.n + C::TH * C::COPY - 1) / (C::TH * C::COPY));
-      const dim3 g(c2.nblk + G.n_patch);
+      const dim3 g(c2.nblk + G.n_patch, (ncol + kMaxCols - 1) / kMaxCols);
       if (record<C::TH>(g, dim3(C::TH), dev::CutColsArgs<D.value, K.value, T, NW>{L, G, x, b, dbuf, xb, c2, ncol}))
         return hipSuccess;
       hipLaunchKernelGGL((dev::k_cut_cols<D.value, K.value, T, NW>), g, dim3(C::TH), 0, s, L, G, x, b, dbuf, xb, c2,
@@ -2697,7 +2769,7 @@ hipError_t launch_cut_cols(int d, int k, const KLevel& L, const CutGroupDev& G, 
     if constexpr (K.value == 1) {
       return go(std::integral_constant<int, 1>{});
     } else {
-      if (D.value == 3 && !t_rec && 3 * (int64_t)G.n_patch < lp.small_cut_launch)
+      if (D.value == 3 && !t_rec && 3 * (int64_t)G.n_patch * ((ncol + kMaxCols - 1) / kMaxCols) < lp.small_cut_launch)
         return go(std::integral_constant<int, D.value == 3 ? 8 : 4>{});
       return go(std::integral_constant<int, 4>{});
     }
@@ -2739,10 +2811,33 @@ hipError_t launch_restrict(int d, int k, const KLevel& Lc, const KLevel& Lf, con
 }
 
 template <typename T>
-hipError_t launch_coarse(const T* inv, const int32_t* dof_node, int n0, const T* b, T* x, int64_t ld, hipStream_t s,
+hipError_t launch_coarse(const T* inv, const int32_t* dof_node, int n, const T* b, T* x, int64_t ld, hipStream_t s,
                          int ncol) {
-  if (record<256>(dim3(blocks(n0, 4), ncol), dim3(256), dev::CoarseArgs<T>{inv, dof_node, n0, b, x, ld})) return hipSuccess;
-  hipLaunchKernelGGL((dev::k_coarse<T>), dim3(blocks(n0, 4), ncol), dim3(256), 0, s, inv, dof_node, n0, b, x, ld);
+  auto go = [&](auto nc) {
+    constexpr int NCOL = decltype(nc)::value;
+    const dim3 g(blocks(n, 4), (ncol + NCOL - 1) / NCOL);
+    if (record<256>(g, dim3(256), dev::CoarseArgs<T, NCOL>{inv, dof_node, n, b, x, ld, ncol})) return hipSuccess;
+    hipLaunchKernelGGL((dev::k_coarse<T, NCOL>), g, dim3(256), 0, s, inv, dof_node, n, b, x, ld, ncol);
+    return hipGetLastError();
+  };
+  if (ncol == 1) return go(std::integral_constant<int, 1>{});
+  return go(std::integral_constant<int, kMaxCols>{});
+}
+
+hipError_t launch_units(const int32_t* dof_node, int64_t n, int64_t c0, int ncol, double* b, int64_t ld,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(dev::k_units, dim3(blocks(n), ncol), dim3(256), 0, s, dof_node, n, c0, b, ld);
+  return hipGetLastError();
+}
+
+hipError_t launch_put_columns(const int32_t* dof_node, int64_t n, int64_t c0, int ncol, const double* x, int64_t ld,
+                              double* m, hipStream_t s) {
+  hipLaunchKernelGGL(dev::k_put_columns, dim3(blocks(n * ncol)), dim3(256), 0, s, dof_node, n, c0, ncol, x, ld, m);
+  return hipGetLastError();
+}
+
+hipError_t launch_round(int64_t n, const double* x, float* y, hipStream_t s) {
+  hipLaunchKernelGGL(dev::k_round, dim3(blocks(n)), dim3(256), 0, s, n, x, y);
   return hipGetLastError();
 }
 
