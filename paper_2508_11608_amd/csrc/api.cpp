@@ -287,6 +287,26 @@ std::vector<T> pack_upper(const std::vector<double>& full, size_t nl) {
   return out;
 }
 
+// The level tables in the kernels' layout; last the jump weights of the m-th
+// derivative on the 2k+1 nodes across a face (psi^(m)(1) of the lower cell minus
+// psi^(m)(0) of the upper one), plain and times the ghost coefficient.
+std::vector<double> pack_tables(const cmg::LevelTables& t, int k) {
+  std::vector<double> p, jm, gj;
+  for (const auto* v : {&t.kcell, &t.mhat, &t.d0, &t.d1, &t.gcoef, &t.fd_s, &t.fd_dinv, &t.p1d, &t.k1s})
+    p.insert(p.end(), v->begin(), v->end());
+  for (int m = 0; m < k; ++m)
+    for (int s = 0; s <= 2 * k; ++s) {
+      double j = 0.0;
+      if (s <= k) j += t.d1[m * (k + 1) + s];
+      if (s >= k) j -= t.d0[m * (k + 1) + s - k];
+      jm.push_back(j);
+      gj.push_back(t.gcoef[m] * j);
+    }
+  p.insert(p.end(), jm.begin(), jm.end());
+  p.insert(p.end(), gj.begin(), gj.end());
+  return p;
+}
+
 template <typename T>
 cmg_status alloc_zero(std::vector<void*>& owned, size_t n, T** dptr) {
   *dptr = nullptr;
@@ -349,9 +369,7 @@ cmg_status upload_all(cmg_problem* P) {
     TRY(upload(own, pack_upper<double>(h.cut_mats, nl), &cpk));
     TRY(upload(own, h.dof_node, &dn));
     const cmg::LevelTables& t = P->H.tables[l];
-    std::vector<double> packed;
-    for (const auto* v : {&t.kcell, &t.mhat, &t.d0, &t.d1, &t.gcoef, &t.fd_s, &t.fd_dinv, &t.p1d, &t.k1s})
-      packed.insert(packed.end(), v->begin(), v->end());
+    const std::vector<double> packed = pack_tables(t, cfg.k);
     if (static_cast<int>(packed.size()) != cmg::tables_size(cfg.dim, cfg.k))
       return fail(CMG_EINVAL, "internal: table layout mismatch");
     TRY(upload(own, packed, &tab));
@@ -362,7 +380,7 @@ cmg_status upload_all(cmg_problem* P) {
     k.cut_packed = cpk;
     k.dof_node = dn;
     k.tables = tab;
-    k.kcell32 = nullptr;
+    k.tables32 = nullptr;
     int32_t *flow, *cgid, *cfaces, *tiles;
     uint8_t* fdir;
     TRY(upload(own, h.face_lower, &flow));
@@ -414,11 +432,35 @@ cmg_status upload_all(cmg_problem* P) {
       G.n_patch = static_cast<int>(g.vertex.size());
       G.n_nodes = static_cast<int64_t>(g.nodes.size());
       if (G.n_patch > 0) {
-        int32_t *off, *nodes, *vert;
+        int32_t *off, *nodes;
         int64_t* ioff;
         double* inv;
-        TRY(upload(own, g.vertex, &vert));
-        G.vertex = vert;
+        // vertex coordinates, and every node's index in its patch's closure
+        std::vector<uint64_t> vpack(g.vertex.size());
+        std::vector<uint16_t> pos(g.nodes.size());
+        for (size_t q = 0; q < g.vertex.size(); ++q) {
+          int64_t V[3] = {0, 0, 0};
+          for (int a = 0, r = g.vertex[q]; a < cfg.dim; ++a) {
+            V[a] = r % (h.N + 1);
+            r /= h.N + 1;
+            vpack[q] |= static_cast<uint64_t>(V[a]) << (21 * a);
+          }
+          for (int e = g.off[q]; e < g.off[q + 1]; ++e) {
+            int64_t r = g.nodes[e], st = 1, at = 0;
+            for (int a = 0; a < cfg.dim; ++a) {
+              at += (r % h.nn - cfg.k * (V[a] - 1)) * st;
+              r /= h.nn;
+              st *= 2 * cfg.k + 1;
+            }
+            pos[e] = static_cast<uint16_t>(at);
+          }
+        }
+        uint64_t* dvp;
+        uint16_t* dpos;
+        TRY(upload(own, vpack, &dvp));
+        TRY(upload(own, pos, &dpos));
+        G.vpack = dvp;
+        G.pos = dpos;
         TRY(upload(own, g.off, &off));
         TRY(upload(own, g.inv_off, &ioff));
         TRY(upload(own, g.nodes, &nodes));
@@ -493,9 +535,9 @@ cmg_status ensure_fp32(cmg_problem* P) {
     const size_t nl = static_cast<size_t>(std::pow(P->H.cfg.k + 1, P->H.cfg.dim));
     TRY(upload(own, pack_upper<float>(h.cut_mats, nl), &cpk));
     d.kl32.cut_packed = cpk;
-    float* kc32;
-    TRY(upload_f32(own, P->H.tables[l].kcell, &kc32));
-    d.kl32.kcell32 = kc32;
+    float* t32;
+    TRY(upload_f32(own, pack_tables(P->H.tables[l], P->H.cfg.k), &t32));
+    d.kl32.tables32 = t32;
     for (int c = 0; c < 8; ++c) {
       if (d.cut32[c].n_patch == 0) continue;
       float* inv;
@@ -1242,11 +1284,11 @@ size_t hierarchy_bytes(const cmg::Hierarchy& H, int flags) {
            8 * (ncm + nt) + 4 * (h.face_lower.size() + h.cell_gid.size() + h.cell_faces.size() +
            h.tiles.size()) + h.face_dir.size();
     b64 += 8 * (3 * static_cast<size_t>(h.n_nodes) + h.face_lower.size() * nw_face);
-    b32 += 4 * (ncm + nl * nl + 3 * static_cast<size_t>(h.n_nodes) + h.face_lower.size() * nw_face);
+    b32 += 4 * (ncm + nt + 3 * static_cast<size_t>(h.n_nodes) + h.face_lower.size() * nw_face);
     for (int c = 0; c < 8; ++c) {
       const cmg::CutPatchGroup& g = h.cut[c];
       const size_t ninv = g.inv_off.empty() ? 0 : static_cast<size_t>(g.inv_off.back());
-      b64 += 4 * (h.int_vertex[c].size() + g.vertex.size() + g.off.size() + g.nodes.size()) + 8 * g.inv_off.size() +
+      b64 += 4 * (h.int_vertex[c].size() + g.off.size()) + 6 * g.nodes.size() + 8 * (g.vertex.size() + g.inv_off.size()) +
              8 * ninv + g.nxt.size() + 6 * g.vertex.size() * (size_t{1} << cfg.dim);
       b32 += 4 * ninv;
       maxn = std::max(maxn, g.nodes.size());

@@ -24,7 +24,7 @@ struct KLevel {
   int64_t n_cut;             // cut cells
   const int32_t* dof_node;   // lattice node of each DoF, ascending
   const double* tables;      // constant tables (uncut stiffness, 1-D factors, FD, prolongation)
-  const float* kcell32;      // FP32 path: the uncut cell stiffness of the tables rounded to FP32 (else null)
+  const float* tables32;     // FP32 path: the tables rounded to FP32 (else null)
   int64_t n_faces;           // ghost faces
   const int32_t* face_lower; // lower cell of every ghost face
   const uint8_t* face_dir;   // its normal direction
@@ -45,7 +45,11 @@ struct KLevel {
   // the uncut cell stiffness (row-major (k+1)^d x (k+1)^d) in the path's precision
   template <typename T>
   __host__ __device__ const T* kcell_t() const {
-    if constexpr (sizeof(T) == 4) return kcell32;
+    return tables_t<T>();
+  }
+  template <typename T>
+  __host__ __device__ const T* tables_t() const {
+    if constexpr (sizeof(T) == 4) return tables32;
     else return tables;
   }
   template <typename T>
@@ -59,7 +63,8 @@ struct CutGroupDev {
   const int32_t* off;        // node offsets, n_patch + 1
   const int64_t* inv_off;    // inverse offsets, n_patch + 1
   const int32_t* nodes;      // lattice nodes of the internal DoFs
-  const int32_t* vertex;     // vertex index of every patch
+  const uint64_t* vpack;     // vertex of every patch, 21 bits per coordinate
+  const uint16_t* pos;       // per node: index in the patch closure ((2k+1)^d nodes, x fastest)
   const int32_t* cell_cut;   // per patch and cell o of its 2^d: cut-cell index, -1 if uncut or outside
   const uint16_t* cell_fg;   // per patch and cell o: flags | ghost bits << 8 (0 outside the box)
   const void* inv;           // symmetric dense inverses, scalar type of the path

@@ -66,7 +66,9 @@ struct Shape {
   static constexpr int T_FDD = T_FDS + NP1 * NP1;
   static constexpr int T_P1D = T_FDD + NP;
   static constexpr int T_K1S = T_P1D + NC1 * N1;
-  static constexpr int T_SIZE = T_K1S + N1 * N1;
+  static constexpr int T_JM = T_K1S + N1 * N1;      // jump weights j_m(s) of the m-th derivative, K x (2K+1)
+  static constexpr int T_GJ = T_JM + K * NC1;       // the same times the ghost coefficient
+  static constexpr int T_SIZE = T_GJ + K * NC1;
 };
 
 // Work index of block b out of n such that the blocks of one XCD take one
@@ -1069,509 +1071,60 @@ struct InteriorStepArgs {
   __device__ void run() const { interior_step_body<D, K, T>(L, verts, nv, x, b); }
 };
 
-// Sizes of the cut-patch kernels (one block per patch).
+// The value that the DPP pattern CTRL brings to this lane: 0x55 q the lane q of
+// its quad, 0x120 + n the lane n below it in its row of 16 (cyclic).
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+// Threads of a large cut-patch launch: a thread per internal node at least.
 template <int D, int K>
-struct CutShape {
-  static constexpr int NF = D * 3 * (1 << (D - 1));       // faces touching a 2^d patch
-  static constexpr int NT = Pow<K + 1, D - 1>::v;         // nodes of a cell face
-  static constexpr int THREADS = Shape<D, K>::NP <= 64 ? 64 : 128;  // one thread per internal node at least
-  static constexpr int COPY = 8;                                      // copy-job items per thread of a copy block
-  static_assert(Shape<D, K>::NP <= THREADS, "a cut-patch block needs a thread per internal node");
+struct CutThreads {
+  static constexpr int v = Shape<D, K>::NP <= 64 ? 64 : 128;
 };
 
-// LDS of one cut-patch block.
-template <int D, int K, typename T>
+// Sizes of the one-column cut step (one block per patch).
+template <int D, int K, typename T, int TH_>
+struct CutShape {
+  using S = Shape<D, K>;
+  static constexpr int TH = TH_, NWV = TH / 64;
+  static constexpr int COPY = 8;                          // copy-job items per thread of a copy block
+  static constexpr int NTC = 1 << (D - 1);                // tangential cells of a direction
+  static constexpr int NPAIR = Pow<2 * K, D>::v;          // (node, cell) pairs
+  static constexpr int SLABS = S::N1;                     // slabs of a cell row along the slowest direction
+  static constexpr int SL = S::NL / SLABS;                // entries per slab
+  static constexpr bool SPLIT = TH > CutThreads<D, K>::v;      // a lane per slab instead of one per pair
+  static constexpr int PS = SPLIT ? SLABS : 1;            // lanes per pair
+  static constexpr int EPT = S::NL / PS;                  // row entries per task
+  static constexpr int NRND = (NPAIR * PS + TH - 1) / TH; // rounds of row tasks
+  static constexpr bool PRE = NRND * EPT * (int)sizeof(T) <= 40 * 4;  // row loads issued before x is staged (more cost a wave per SIMD)
+  static constexpr int GS = SPLIT && S::NP > 1 ? 4 : 1;   // lanes per row of the local solve
+  static constexpr int NACC = S::NP <= 32 ? 4 : 8;        // partial sums of a row of the local solve
+  static constexpr int JP = (S::NP + NACC - 1) / NACC * NACC / GS;  // entries of a row per lane
+  static constexpr int RSN = (S::NP + 31) / 32 * 32;      // residual rows, padded with zeros
+  static constexpr int HT = Pow<2 * K, D - 1>::v;         // (tangential cell, internal node) choices
+  static constexpr int HS = S::NP1 * HT;                  // ghost rows per direction
+  static constexpr int GR = D == 3 ? (3 + NWV - 1) / NWV : 1;  // directions per wave
+  static_assert(S::NP * GS <= TH, "a cut-patch block needs the lanes of every row of the local solve");
+};
+
+template <int D, int K, typename T, int TH>
 struct CutSmem {
   using S = Shape<D, K>;
-  using C = CutShape<D, K>;
-  double tab[S::T_D1 + K * S::N1 + K - S::T_MHAT];  // mhat | d0 | d1 | gc
-  static constexpr int NPAIR = Pow<2 * K, D>::v;  // (node, cell) pairs of a patch, see cut_patch_ax
-  // FP64 Q2 in 3-D stages the halo of the ghost faces too (measured faster
-  // there; elsewhere the extra staging costs more than the scattered loads)
-  static constexpr bool kHalo = sizeof(T) == 8 && D == 3 && K == 2;
-  static constexpr int NH = K * Pow<S::NC1, D - 1>::v;  // nodes of one halo slab
-  static constexpr int NE = S::NC + (kHalo ? 2 * D * NH : 0);
-  T xs[NE];  // x on the patch closure, then the halo slabs (dir, side), see cut_patch_ax
-  T Wf[C::NF][K][C::NT];
-  T parts[NPAIR];
-  int16_t slot[S::NP];  // row of the patch's node at each internal position, -1 if absent
-  uint8_t cfl[1 << D], cgh[1 << D];
-  int32_t ccut[1 << D];
+  using C = CutShape<D, K, T, TH>;
+  T xs[S::NC];                    // x on the patch closure
+  T parts[C::NPAIR * C::PS];      // cell rows
+  T H[D][C::HS];                  // ghost rows
+  T rs[C::RSN];                   // residual rows
+  T jg[2 * K * S::NC1];           // jump weights j_m, gc_m j_m
+  int16_t pos[S::NP];             // closure index of every row
 };
-
-// Patch set-up of the cut-patch kernel: level tables, the 2^d cells around the
-// vertex (flags, ghost bits, cut ids) and the vertex coordinates.  Returns the
-// lattice node of the thread's internal node (tid < nj), else -1; the slot
-// table is filled by cut_patch_ax.
-template <int D, int K, typename T>
-__device__ int cut_patch_setup(const KLevel& L, const CutGroupDev& G, int gp, CutSmem<D, K, T>& sm, int* V) {
-  using S = Shape<D, K>;
-  constexpr int N1 = S::N1, NCELL = 1 << D;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  for (int i = tid; i < S::T_D1 + K * N1 + K - S::T_MHAT; i += nth) sm.tab[i] = L.tables[S::T_MHAT + i];
-  for (int i = tid; i < S::NP; i += nth) sm.slot[i] = -1;
-  const int off = G.off[gp];
-  const int nj = G.off[gp + 1] - off;
-  const int NV = L.N + 1;
-  {
-    int vr = G.vertex[gp];
-#pragma unroll
-    for (int a = 0; a < D; ++a) { V[a] = vr % NV; vr /= NV; }
-  }
-  if (tid < NCELL) {  // the patch's cells, indexed by the patch (no wait for its vertex)
-    const uint16_t fg = G.cell_fg[(int64_t)gp * NCELL + tid];
-    sm.cfl[tid] = static_cast<uint8_t>(fg & 0xff);
-    sm.cgh[tid] = static_cast<uint8_t>(fg >> 8);
-    sm.ccut[tid] = G.cell_cut[(int64_t)gp * NCELL + tid];
-  }
-  const int node = tid < nj ? G.nodes[off + tid] : -1;  // used after the staging loads are issued
-  __syncthreads();  // tables, slot initialisation and cells visible
-  return node;
-}
-
-// (A x) at the internal node of thread tid (tid < nj; other threads return 0)
-// for the patch prepared by cut_patch_setup.  x on the patch closure is staged
-// in LDS.  The jumps J_m = d^m-trace(lower) - d^m-trace(upper) of every ghost
-// face touching the patch are formed from x in memory (the nodes of both
-// cells of the face, which can reach one cell layer beyond the closure) while
-// the closure loads are in flight, and contracted with the face mass once per
-// face.  The rows are then split into (node, cell) pairs: along each direction
-// a node at patch coordinate p in 1..2k-1 lies in cell layer 0 (p <= k) and/or
-// 1 (p >= k), which gives 2k (p, layer) choices per direction and (2k)^d pairs,
-// enumerated arithmetically (absent nodes and inactive cells give zero).  A
-// pair needs its cell row (uncut stiffness or cut-cell matrix) and k (k+1)^{d-1}
-// terms per incident ghost face; each node sums its pairs in a fixed order.
-// xold receives x at the thread's node.  Called by all threads of the block
-// (it synchronises); the LDS buffers are reused on the next call.
-template <int D, int K, typename T, int TH>
-__device__ T cut_patch_ax(const KLevel& L, int nj, const int* V, int node, int* pi, const T* __restrict__ x,
-                          const T* __restrict__ b, CutSmem<D, K, T>& sm, T* xold, T* bval) {
-  using S = Shape<D, K>;
-  using C = CutShape<D, K>;
-  constexpr int N1 = S::N1, NL = S::NL, NC = S::NC, W1 = S::NC1, NF = C::NF, NT = C::NT;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const double* mh = sm.tab;
-  const double* d0 = sm.tab + (S::T_D0 - S::T_MHAT);
-  const double* d1 = sm.tab + (S::T_D1 - S::T_MHAT);
-  const double* gc = sm.tab + (S::T_GC - S::T_MHAT);
-  if constexpr (CutSmem<D, K, T>::kHalo) {
-  // Stage x on the closure and on the halo slabs that ghost faces on the
-  // patch boundary need: slab (a, side) holds the k node layers beyond the
-  // closure along direction a (cell V-2 for side 0, V+1 for side 1) over the
-  // closure's tangential range, node layers fastest.  Coordinates are relative
-  // to the closure origin k (V-1).
-  constexpr int NH = CutSmem<D, K, T>::NH, NE = CutSmem<D, K, T>::NE;
-  uint32_t need = 0;  // bit 2a+side: slab (a, side) is read by a ghost face
-#pragma unroll
-  for (int o = 0; o < (1 << D); ++o) {
-    const uint8_t g = sm.cgh[o];
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (((o >> a) & 1) == 0 && (g & (1 << (2 * a)))) need |= 1u << (2 * a);
-      if (((o >> a) & 1) == 1 && (g & (1 << (2 * a + 1)))) need |= 1u << (2 * a + 1);
-    }
-  }
-  constexpr int NIT = (NE + TH - 1) / TH;
-  T v[NIT];
-#pragma unroll
-  for (int u = 0; u < NIT; ++u) {
-    const int e = tid + TH * u;
-    v[u] = 0;
-    int rr[3];
-    bool ld = e < NE;
-    if (e < NC) {
-      int r = e;
-#pragma unroll
-      for (int a = 0; a < D; ++a) { rr[a] = r % W1; r /= W1; }
-    } else if (ld) {
-      const int h = e - NC, slab = h / NH, dir = slab >> 1, side = slab & 1;
-      int r = h % NH;
-      const int layer = r % K;
-      r /= K;
-      ld = ((need >> slab) & 1) && !L.ghost_local;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        if (a == dir) {
-          rr[a] = side ? 2 * K + 1 + layer : layer - K;
-        } else {
-          rr[a] = r % W1;
-          r /= W1;
-        }
-      }
-    }
-    if (ld) {
-      int I[3];
-      bool in = true;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        I[a] = K * (V[a] - 1) + rr[a];
-        in = in && I[a] >= 0 && I[a] < L.nn;
-      }
-      if (in) v[u] = x[lat(D, L.nn, I)];
-    }
-  }
-  // the thread's node (its load was issued in the set-up): patch coordinates
-  // 1 .. 2k-1, row in the slot table, and b, whose load overlaps the staging
-  if (tid < nj) {
-    int r = node, pos = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      pi[a] = r % L.nn - K * (V[a] - 1);
-      r /= L.nn;
-    }
-#pragma unroll
-    for (int a = D - 1; a >= 0; --a) pos = pos * S::NP1 + (pi[a] - 1);
-    sm.slot[pos] = static_cast<int16_t>(tid);
-    *bval = b[node];
-  }
-#pragma unroll
-  for (int u = 0; u < NIT; ++u) {
-    const int e = tid + TH * u;
-    if (e < NE) sm.xs[e] = v[u];
-  }
-  __syncthreads();
-  // mass-contracted jumps W_m(i_t) of every ghost face touching the patch:
-  // face (dir, plane 0..2, tangential cell t), plane p between cell layers p-1, p
-  for (int task = tid; task < NF * K; task += nth) {
-    const int m = task % K;
-    const int f = task / K;
-    const int dir = f / (3 << (D - 1));
-    const int plane = (f >> (D - 1)) % 3;
-    const int t = f & ((1 << (D - 1)) - 1);
-    int o = 0, tb = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (a == dir) continue;
-      o |= ((t >> tb) & 1) << a;
-      ++tb;
-    }
-    bool ghost;
-    if (plane == 0) ghost = sm.cgh[o] & (1 << (2 * dir));               // lower face of layer 0
-    else if (plane == 1) ghost = sm.cgh[o] & (1 << (2 * dir + 1));      // between layers 0 and 1
-    else ghost = sm.cgh[o | (1 << dir)] & (1 << (2 * dir + 1));         // upper face of layer 1
-    if (!ghost) continue;
-    // closure strides of the normal (sd) and tangential (s0, s1) directions
-    // and the tangential cell offsets (K t0, K t1) of the face
-    int sd = 1, s0 = 0, s1 = 0, k0 = 0, k1 = 0, tb2 = 0, st = 1;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (a == dir) {
-        sd = st;
-      } else if (tb2 == 0) {
-        s0 = st;
-        k0 = K * ((t >> tb2) & 1);
-        ++tb2;
-      } else {
-        s1 = st;
-        k1 = K * ((t >> tb2) & 1);
-        ++tb2;
-      }
-      st *= W1;
-    }
-    const int hbase = NC + 2 * dir * NH;
-    T dl[N1], du[N1];
-#pragma unroll
-    for (int bd = 0; bd <= K; ++bd) {
-      dl[bd] = (T)d1[m * N1 + bd];
-      du[bd] = (T)d0[m * N1 + bd];
-    }
-    // LDS index of the node with normal coordinate rd (first node of the lower
-    // cell at K (plane - 1)) and tangential coordinates (r0, r1)
-    auto idx = [&](int rd, int r0, int r1) {
-      if (rd >= 0 && rd <= 2 * K) return r0 * s0 + r1 * s1 + rd * sd;
-      const int side = rd > 2 * K;
-      return hbase + side * NH + (r0 + W1 * r1) * K + (side ? rd - 2 * K - 1 : rd + K);
-    };
-    T J[NT];
-#pragma unroll
-    for (int bt = 0; bt < NT; ++bt) {
-      const int r0 = k0 + bt % N1, r1 = D == 3 ? k1 + bt / N1 : 0;
-      T acc0 = 0, acc1 = 0;
-#pragma unroll
-      for (int bd = 0; bd <= K; ++bd) {
-        acc0 += dl[bd] * sm.xs[idx(K * (plane - 1) + bd, r0, r1)];
-        acc1 += du[bd] * sm.xs[idx(K * plane + bd, r0, r1)];
-      }
-      J[bt] = acc0 - acc1;
-    }
-    T mm[N1 * N1];
-#pragma unroll
-    for (int i = 0; i < N1 * N1; ++i) mm[i] = (T)mh[i];
-    if (D == 2) {
-#pragma unroll
-      for (int it = 0; it < N1; ++it) {
-        T acc = 0;
-#pragma unroll
-        for (int bt = 0; bt < N1; ++bt) acc += mm[it * N1 + bt] * J[bt];
-        sm.Wf[f][m][it] = acc;
-      }
-    } else {
-      // (Mhat x Mhat) J by two 1-D contractions
-      T H[NT];
-#pragma unroll
-      for (int b1 = 0; b1 < N1; ++b1)
-#pragma unroll
-        for (int i0 = 0; i0 < N1; ++i0) {
-          T acc = 0;
-#pragma unroll
-          for (int b0 = 0; b0 < N1; ++b0) acc += mm[i0 * N1 + b0] * J[b0 + N1 * b1];
-          H[i0 + N1 * b1] = acc;
-        }
-#pragma unroll
-      for (int i1 = 0; i1 < N1; ++i1)
-#pragma unroll
-        for (int i0 = 0; i0 < N1; ++i0) {
-          T acc = 0;
-#pragma unroll
-          for (int b1 = 0; b1 < N1; ++b1) acc += mm[i1 * N1 + b1] * H[i0 + N1 * b1];
-          sm.Wf[f][m][i0 + N1 * i1] = acc;
-        }
-    }
-  }
-  } else {
-  const int64_t nn = L.nn;
-  // closure loads first (stored to LDS after the face jumps; blockDim == THREADS)
-  constexpr int NIT = (NC + TH - 1) / TH;
-  T v[NIT];
-#pragma unroll
-  for (int u = 0; u < NIT; ++u) {
-    const int e = tid + TH * u;
-    v[u] = 0;
-    if (e < NC) {
-      int I[3], r = e;
-      bool in = true;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        I[a] = K * (V[a] - 1) + r % W1;
-        r /= W1;
-        in = in && I[a] >= 0 && I[a] < L.nn;
-      }
-      if (in) v[u] = x[lat(D, L.nn, I)];
-    }
-  }
-  // the thread's node (its load was issued in the set-up): patch coordinates
-  // 1 .. 2k-1, row in the slot table, and b, whose load overlaps the staging
-  if (tid < nj) {
-    int r = node, pos = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      pi[a] = r % L.nn - K * (V[a] - 1);
-      r /= L.nn;
-    }
-#pragma unroll
-    for (int a = D - 1; a >= 0; --a) pos = pos * S::NP1 + (pi[a] - 1);
-    sm.slot[pos] = static_cast<int16_t>(tid);
-    *bval = b[node];
-  }
-  // mass-contracted jumps W_m(i_t) of every ghost face touching the patch:
-  // face (dir, plane 0..2, tangential cell t), plane p between cell layers p-1, p
-  for (int task = tid; task < NF * K; task += nth) {
-    const int m = task % K;
-    const int f = task / K;
-    const int dir = f / (3 << (D - 1));
-    const int plane = (f >> (D - 1)) % 3;
-    const int t = f & ((1 << (D - 1)) - 1);
-    int o = 0, tb = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (a == dir) continue;
-      o |= ((t >> tb) & 1) << a;
-      ++tb;
-    }
-    bool ghost;
-    if (plane == 0) ghost = sm.cgh[o] & (1 << (2 * dir));               // lower face of layer 0
-    else if (plane == 1) ghost = sm.cgh[o] & (1 << (2 * dir + 1));      // between layers 0 and 1
-    else ghost = sm.cgh[o | (1 << dir)] & (1 << (2 * dir + 1));         // upper face of layer 1
-    if (!ghost) continue;
-    // first node of the lower cell of the face, lattice strides of the
-    // tangential directions and of the normal one (a ghost face has both of
-    // its cells in the background box, so every node read is in the lattice)
-    int I[3], tb2 = 0;
-    int64_t st0 = 0, st1 = 0, sn = 1, sa = 1;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (a == dir) {
-        I[a] = K * (V[a] - 2 + plane);
-        sn = sa;
-      } else {
-        I[a] = K * (V[a] - 1 + ((t >> tb2) & 1));
-        if (tb2 == 0) st0 = sa; else st1 = sa;
-        ++tb2;
-      }
-      sa *= nn;
-    }
-    const int64_t base = lat(D, L.nn, I);
-    // patch-local residual: the lower cell of a plane-0 face and the upper
-    // cell of a plane-2 face lie outside the patch; their nodes beyond the
-    // closure (normal layers other than the shared face) get weight zero (the
-    // loads stay unconditional)
-    const bool lo_out = L.ghost_local && plane == 0, hi_out = L.ghost_local && plane == 2;
-    T dl[N1], du[N1];
-#pragma unroll
-    for (int bd = 0; bd <= K; ++bd) {
-      dl[bd] = (lo_out && bd < K) ? (T)0 : (T)d1[m * N1 + bd];
-      du[bd] = (hi_out && bd > 0) ? (T)0 : (T)d0[m * N1 + bd];
-    }
-    T J[NT];
-#pragma unroll
-    for (int bt = 0; bt < NT; ++bt) {
-      const int64_t el = base + (bt % N1) * st0 + (D == 3 ? (bt / N1) * st1 : 0);
-      T acc0 = 0, acc1 = 0;
-#pragma unroll
-      for (int bd = 0; bd <= K; ++bd) {
-        acc0 += dl[bd] * x[el + bd * sn];
-        acc1 += du[bd] * x[el + (bd + K) * sn];
-      }
-      J[bt] = acc0 - acc1;
-    }
-    T mm[N1 * N1];
-#pragma unroll
-    for (int i = 0; i < N1 * N1; ++i) mm[i] = (T)mh[i];
-    if (D == 2) {
-#pragma unroll
-      for (int it = 0; it < N1; ++it) {
-        T acc = 0;
-#pragma unroll
-        for (int bt = 0; bt < N1; ++bt) acc += mm[it * N1 + bt] * J[bt];
-        sm.Wf[f][m][it] = acc;
-      }
-    } else {
-      // (Mhat x Mhat) J by two 1-D contractions
-      T H[NT];
-#pragma unroll
-      for (int b1 = 0; b1 < N1; ++b1)
-#pragma unroll
-        for (int i0 = 0; i0 < N1; ++i0) {
-          T acc = 0;
-#pragma unroll
-          for (int b0 = 0; b0 < N1; ++b0) acc += mm[i0 * N1 + b0] * J[b0 + N1 * b1];
-          H[i0 + N1 * b1] = acc;
-        }
-#pragma unroll
-      for (int i1 = 0; i1 < N1; ++i1)
-#pragma unroll
-        for (int i0 = 0; i0 < N1; ++i0) {
-          T acc = 0;
-#pragma unroll
-          for (int b1 = 0; b1 < N1; ++b1) acc += mm[i1 * N1 + b1] * H[i0 + N1 * b1];
-          sm.Wf[f][m][i0 + N1 * i1] = acc;
-        }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < NIT; ++u) {
-    const int e = tid + TH * u;
-    if (e < NC) sm.xs[e] = v[u];
-  }
-  }
-  __syncthreads();
-  // (node, cell) pairs
-  constexpr int NPAIR = CutSmem<D, K, T>::NPAIR;
-  for (int t = tid; t < NPAIR; t += nth) {
-    int p[3], o = 0, pos = 0;
-    {
-      int r = t;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const int j = r % (2 * K);
-        r /= 2 * K;
-        p[a] = j < K ? j + 1 : j;
-        o |= (j >= K ? 1 : 0) << a;
-      }
-#pragma unroll
-      for (int a = D - 1; a >= 0; --a) pos = pos * S::NP1 + (p[a] - 1);
-    }
-    T part = 0;
-    const uint8_t f = sm.cfl[o];
-    if (sm.slot[pos] >= 0 && (f & 1)) {
-      int il[3];
-#pragma unroll
-      for (int a = 0; a < D; ++a) il[a] = p[a] - K * ((o >> a) & 1);
-      int iloc = il[0] + N1 * il[1];
-      if (D == 3) iloc += N1 * N1 * il[2];
-      int xb = K * (o & 1) + W1 * K * ((o >> 1) & 1);  // closure index of the cell's first node
-      if (D == 3) xb += W1 * W1 * K * ((o >> 2) & 1);
-      // dot product of the cell row with x, one partial sum per x-row of the cell
-      constexpr int NRW = N1 * (D == 3 ? N1 : 1);
-      T acc[NRW];
-#pragma unroll
-      for (int a = 0; a < NRW; ++a) acc[a] = 0;
-      if (f & 2) {
-        const T* row = L.cut_mats_t<T>() + ((int64_t)sm.ccut[o] * NL + iloc) * NL;
-#pragma unroll
-        for (int bq = 0; bq < NL; ++bq) {
-          const int b0 = bq % N1, b12 = bq / N1;
-          const int xi = xb + b0 + W1 * (b12 % N1) + (D == 3 ? W1 * W1 * (b12 / N1) : 0);
-          acc[b12] += row[bq] * sm.xs[xi];
-        }
-      } else {
-        const T* row = L.kcell_t<T>() + S::T_KCELL + iloc * NL;
-#pragma unroll
-        for (int bq = 0; bq < NL; ++bq) {
-          const int b0 = bq % N1, b12 = bq / N1;
-          const int xi = xb + b0 + W1 * (b12 % N1) + (D == 3 ? W1 * W1 * (b12 / N1) : 0);
-          acc[b12] += row[bq] * sm.xs[xi];
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < NRW; ++a) part += acc[a];
-      const uint8_t g = sm.cgh[o];
-      if (g) {
-#pragma unroll
-        for (int dir = 0; dir < D; ++dir)
-#pragma unroll
-          for (int side = 0; side < 2; ++side) {
-            if (!(g & (1 << (2 * dir + side)))) continue;
-            const int plane = ((o >> dir) & 1) + side;
-            int tt = 0, tb = 0, it = 0, st = 1;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-              if (a == dir) continue;
-              tt |= ((o >> a) & 1) << tb;
-              ++tb;
-              it += il[a] * st;
-              st *= N1;
-            }
-            const int fi = (dir * 3 + plane) * (1 << (D - 1)) + tt;
-#pragma unroll
-            for (int m = 0; m < K; ++m) {
-              const double sg = gc[m] * (side == 1 ? d1[m * N1 + il[dir]] : -d0[m * N1 + il[dir]]);
-              part += (T)sg * sm.Wf[fi][m][it];
-            }
-          }
-      }
-    }
-    sm.parts[t] = part;
-  }
-  __syncthreads();
-  T ax = 0;
-  if (tid < nj) {
-    // x at the node itself (closure index = patch coordinates)
-    *xold = sm.xs[pi[0] + W1 * pi[1] + (D == 3 ? W1 * W1 * pi[2] : 0)];
-    // the node's pairs: per direction index j = p - 1 (layer 0, p <= k) and
-    // j = p (layer 1, p >= k), in increasing pair index
-    int jlo[3], jn[3];
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      jlo[a] = pi[a] <= K ? pi[a] - 1 : pi[a];
-      jn[a] = pi[a] == K ? 2 : 1;
-    }
-    const int ncomb = jn[0] * jn[1] * (D == 3 ? jn[2] : 1);
-    for (int comb = 0; comb < ncomb; ++comb) {
-      int t = 0, r = comb, st = 1;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const int sel = r % jn[a];
-        r /= jn[a];
-        t += (jlo[a] + sel) * st;
-        st *= 2 * K;
-      }
-      ax += sm.parts[t];
-    }
-  }
-  __syncthreads();  // the buffers may be restaged by the next call
-  return ax;
-}
 
 // Cut patches, phase 1: residual on the internal nodes and dense local solve
 // d_j = A_j^{-1} r_j (GEMV with the symmetric inverse), one block per patch
@@ -1580,17 +1133,37 @@ __device__ T cut_patch_ax(const KLevel& L, int nj, const int* V, int node, int* 
 // otherwise xb = x + d_j on the patch's internal DoFs (same-coloured patches
 // share none), and the first cj.nblk blocks copy the nodes of the copy job
 // from x to xb instead of solving a patch.
+//
+// One patch is a chain of short phases, so what counts is its length and the
+// instructions in it:
+//   - the patch's record (offsets, vertex, flags, cut ids) is scalar loads of
+//     one round trip; x, b, the node layers beyond the closure that ghost faces
+//     reach and (where they fit in registers) the cell rows are requested
+//     before anything is waited for;
+//   - cell rows: along each direction an internal node at patch coordinate p in
+//     1..2k-1 lies in cell layer 0 (p <= k) and/or 1 (p >= k), which gives 2k
+//     (p, layer) choices per direction and (2k)^d (node, cell) pairs, a lane each;
+//   - ghost faces by sum factorisation as in k_cut_cols: a wave takes a
+//     direction, 16 lanes a tangential cell, a lane one node line;
+//   - every node sums its pairs and ghost rows in a fixed order with all LDS
+//     reads in flight, and a lane takes a row of the local solve.
+// Launches that leave CUs idle (coarse levels) take more threads: a lane per
+// slab of a pair's cell row and 4 lanes per row of the local solve, whose
+// entries are requested at the start.  Every sum keeps its order, so results
+// do not depend on the choice.  128^3 ball, Q2, finest step (11,866 patches): FP64
+// 58.5 -> 48.1 us, FP32 38.3 -> 28.7 us; 740 patches FP64 10.7 -> 8.8 us; union of 8
+// spheres, Q3, 40 patches 25.0 -> 13.9 us.  The finest step is bound by its reads
+// (cut-cell rows in 216-byte pieces and inverses, 180 MB), a small one by four
+// dependent round trips to memory and the launch.
 template <int D, int K, typename T, int TH>
-__global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G,
-                                                                        const T* __restrict__ x,
-                                                                        const T* __restrict__ b,
-                                                                        T* __restrict__ dbuf, T* __restrict__ xb,
-                                                                        CopyJob cj) {
+__global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G, const T* __restrict__ x,
+                                                  const T* __restrict__ b, T* __restrict__ dbuf, T* __restrict__ xb,
+                                                  CopyJob cj) {
   using S = Shape<D, K>;
-  using C = CutShape<D, K>;
-  __shared__ CutSmem<D, K, T> sm;
-  constexpr int RSN = (S::NP + 31) / 32 * 32;  // residual rows, padded with zeros to whole GEMV batches
-  __shared__ T rs[RSN];
+  using C = CutShape<D, K, T, TH>;
+  constexpr int N1 = S::N1, NL = S::NL, NC = S::NC, W1 = S::NC1, NP = S::NP, NP1 = S::NP1, NCELL = 1 << D;
+  constexpr int NTC = C::NTC;
+  __shared__ CutSmem<D, K, T, TH> sm;
   const int tid = threadIdx.x;
   x += blockIdx.y * L.n_nodes;
   b += blockIdx.y * L.n_nodes;
@@ -1613,50 +1186,320 @@ __global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G,
     return;
   }
   const int gp = xcd_block(blockIdx.x - cj.nblk, gridDim.x - cj.nblk);
-  int V[3] = {0, 0, 0}, pi[3] = {0, 0, 0};
-  const int node = cut_patch_setup<D, K, T>(L, G, gp, sm, V);
-  const int off = G.off[gp];
-  const int nj = G.off[gp + 1] - off;
-  T xold = 0, bval = 0;
-  const T ax = cut_patch_ax<D, K, T, TH>(L, nj, V, node, pi, x, b, sm, &xold, &bval);
-  if (tid < nj) rs[tid] = bval - ax;
-  for (int e = nj + tid; e < RSN; e += TH) rs[e] = 0;
-  __syncthreads();
-  // d = A_j^{-1} r: thread i takes row i (= column i, the inverse is symmetric)
-  // (blockDim >= NP >= nj).  Small patches issue all loads of the row at once,
-  // larger ones in batches; loads past the last row re-read it (their
-  // residual entries are zero), so every load of a batch is issued unconditionally.
-  if (tid >= nj) return;
-  const T* inv = G.inv_t<T>() + G.inv_off[gp];
-  T dv;
-  if constexpr (S::NP <= 32) {
-    T v[S::NP];
+  // the patch's record
+  const int off = G.off[gp], nj = G.off[gp + 1] - off;
+  const int64_t ioff = G.inv_off[gp];
+  const uint64_t vp = G.vpack[gp];
+  // flags of the 2^d cells, 4 cells a word
+  const uint64_t fga = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4)];
+  const uint64_t fgb = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4) + NCELL / 4 - 1];
+  auto cell_fg = [fga, fgb](int o) { return static_cast<int>((o >= 4 ? fgb : fga) >> (16 * (o & 3))) & 0xffff; };
+  const int nn = L.nn, nn2 = nn * nn;
+  int V[3] = {1, 1, 1};
+  bool inside = true;  // the closure lies in the lattice
 #pragma unroll
-    for (int j = 0; j < S::NP; ++j) v[j] = inv[(int64_t)(j < nj ? j : nj - 1) * nj + tid];
-    T acc[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < S::NP; ++j) acc[j % 4] += v[j] * rs[j];
-    dv = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  } else {
-    // batches of 32 (FP32) or 16 (FP64) independent loads
-    constexpr int NB = sizeof(T) == 4 ? 32 : 16;
-    const int i = tid;
-    T acc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] = 0;
-    for (int j = 0; j < nj; j += NB) {
-      T v[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) v[u] = inv[(int64_t)(j + u < nj ? j + u : nj - 1) * nj + i];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) acc[u % 8] += v[u] * rs[j + u];
-    }
-    dv = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  for (int a = 0; a < D; ++a) {
+    V[a] = static_cast<int>(vp >> (21 * a)) & 0x1fffff;
+    inside = inside && V[a] >= 1 && V[a] < L.N;
   }
+  const int cbase = K * (V[0] - 1) + nn * (K * (V[1] - 1)) + (D == 3 ? nn2 * (K * (V[2] - 1)) : 0);
+  x += cbase;  // from here on relative to the closure's corner
+  b += cbase;
+  // lattice offset of a closure node
+  auto loff = [&](int q) {
+    return q % W1 + nn * ((q / W1) % W1) + (D == 3 ? nn2 * (q / (W1 * W1)) : 0);
+  };
+  // closure
+  constexpr int NIT = (NC + TH - 1) / TH;
+  T v[NIT];
+#pragma unroll
+  for (int u = 0; u < NIT; ++u) {
+    const int e = tid + TH * u < NC ? tid + TH * u : NC - 1;
+    if (inside) {
+      v[u] = x[loff(e)];
+    } else {  // nodes beyond the lattice count as zero
+      int r = e;
+      bool in = true;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const int I = K * (V[a] - 1) + r % W1;
+        r /= W1;
+        in = in && I >= 0 && I < nn;
+      }
+      v[u] = in ? x[loff(e)] : (T)0;
+    }
+  }
+  const int bsafe = K + nn * K + (D == 3 ? nn2 * K : 0);  // the patch's vertex node
+  // ghost faces: a wave per direction in 3-D (lane: tangential cell, b1, b0), all of them in the first wave in 2-D
+  const int lane = tid % 64, wave = C::NWV == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / 64);
+  const int b0 = lane % 4, b1 = D == 3 ? (lane / 4) % 4 : 0;
+  const int t0 = D == 3 ? (lane / 16) & 1 : (lane / 4) & 1, t1 = D == 3 ? lane / 32 : 0;
+  T lo[C::GR][K], hi[C::GR][K];
+  bool gf[C::GR][3];
+#pragma unroll
+  for (int g = 0; g < C::GR; ++g) {
+    const int dir = D == 3 ? wave + g * C::NWV : (lane / 8) & 1;
+    const bool mine = D == 3 ? dir < 3 : tid < 16;
+    const int d0 = dir == 0 ? 1 : 0, d1 = dir == 2 ? 1 : 2;  // tangential directions (d1: 3-D only)
+    const int o = (t0 << d0) | (D == 3 ? t1 << d1 : 0);
+    const int glo = cell_fg(o) >> 8, ghi = cell_fg((o | 1 << dir) & (NCELL - 1)) >> 8;
+    const bool on = mine && b0 < N1 && b1 < N1;
+    gf[g][0] = on && (glo & (1 << (2 * dir)));
+    gf[g][1] = on && (glo & (2 << (2 * dir)));
+    gf[g][2] = on && (ghi & (2 << (2 * dir)));
+    const int gd = dir == 0 ? 1 : dir == 1 ? nn : nn2, g0 = d0 == 0 ? 1 : nn, g1 = D == 3 ? (d1 == 1 ? nn : nn2) : 0;
+    const T* xg = x + ((K * t0 + b0) * g0 + (K * t1 + b1) * g1);
+    // patch-local residual: x beyond the closure counts as zero
+    const bool flo = gf[g][0] && !L.ghost_local, fhi = gf[g][2] && !L.ghost_local;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      // a lane without the face reads a node that is in the lattice anyway
+      const T l = *(flo ? xg + (q - K) * gd : b + bsafe), h = *(fhi ? xg + (2 * K + 1 + q) * gd : b + bsafe);
+      lo[g][q] = flo ? l : (T)0;
+      hi[g][q] = fhi ? h : (T)0;
+    }
+  }
+  // entries of the 1-D mass for the tangential directions (see k_cut_cols)
+  const T* tab = L.tables_t<T>();
+  constexpr int NJG = 2 * K * W1;  // jump weights, plain and times the ghost coefficients
+  const T jgv = tab[S::T_JM + (tid < NJG ? tid : 0)];
+  T w0[4], w1[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int q1 = (b1 - q) & 3, r0 = b0 < N1 ? b0 : 0, r1 = b1 < N1 ? b1 : 0;
+    const T e0 = tab[S::T_MHAT + r0 * N1 + (q < N1 ? q : 0)], e1 = tab[S::T_MHAT + r1 * N1 + (q1 < N1 ? q1 : 0)];
+    w0[q] = b0 < N1 && q < N1 ? e0 : (T)0;
+    w1[q] = b1 < N1 && q1 < N1 ? e1 : (T)0;
+  }
+  // row tasks: pair t / PS, slabs from (t % PS) SLABS / PS on
+  auto pair_of = [&](int pt, int& o, int& iloc) {
+    o = 0;
+    iloc = 0;
+    int r = pt, st = 1;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const int j = r % (2 * K);
+      r /= 2 * K;
+      o |= (j >= K ? 1 : 0) << a;
+      iloc += (j < K ? j + 1 : j - K) * st;
+      st *= N1;
+    }
+  };
+  auto row_ptr = [&](int t) {
+    int o, iloc;
+    pair_of(t / C::PS, o, iloc);
+    const int cut = G.cell_cut[(int64_t)gp * NCELL + o];
+    const T* m = cell_fg(o) & 2 ? L.cut_mats_t<T>() + (int64_t)cut * NL * NL : L.kcell_t<T>() + S::T_KCELL;
+    return m + iloc * NL + (C::PS > 1 ? (t % C::PS) * C::SL : 0);
+  };
+  T row[C::PRE ? C::NRND : 1][C::EPT];
+  if constexpr (C::PRE) {
+#pragma unroll
+    for (int u = 0; u < C::NRND; ++u) {
+      const int t = tid + TH * u;
+      if (t < C::NPAIR * C::PS) {
+        const T* m = row_ptr(t);
+#pragma unroll
+        for (int e = 0; e < C::EPT; ++e) row[u][e] = m[e];
+      }
+    }
+  }
+  // the thread's node: closure index (from the record unless the patch is full), b
+  int pos = 0;
+  T bval = 0;
+  if (tid < nj) {
+    if (nj == NP)  // uniform
+      pos = tid % NP1 + 1 + W1 * ((tid / NP1) % NP1 + 1) + (D == 3 ? W1 * W1 * (tid / (NP1 * NP1) + 1) : 0);
+    else
+      pos = G.pos[off + tid];
+    bval = b[loff(pos)];
+    sm.pos[tid] = static_cast<int16_t>(pos);
+  }
+  // the lane's part of its row of the local solve
+  const int gi = tid / C::GS, gu = tid % C::GS;
+  const T* inv = G.inv_t<T>() + ioff + (gi < nj ? gi : 0);
+  T iv[C::SPLIT ? C::JP : 1];
+  if constexpr (C::SPLIT) {
+#pragma unroll
+    for (int e = 0; e < C::JP; ++e) {
+      const int j = gu + C::GS * e;
+      iv[e] = inv[(int64_t)(j < nj ? j : nj - 1) * nj];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < NIT; ++u) {
+    const int e = tid + TH * u;
+    if (e < NC) sm.xs[e] = v[u];
+  }
+  if (tid < NJG) sm.jg[tid] = jgv;
+  __syncthreads();
+  // ghost rows
+  uint32_t gmask = 0;  // bit dir 2^(d-1) + t: that (direction, tangential cell) has a face
+#pragma unroll
+  for (int dt = 0; dt < D * NTC; ++dt) {
+    const int dir = dt / NTC, t = dt % NTC;
+    const int d0 = dir == 0 ? 1 : 0, d1 = dir == 2 ? 1 : 2;
+    const int o = ((t & 1) << d0) | (D == 3 ? (t >> 1) << d1 : 0);
+    if (((cell_fg(o) >> 8) & (3 << (2 * dir))) || ((cell_fg(o | 1 << dir) >> 8) & (2 << (2 * dir)))) gmask |= 1u << dt;
+  }
+#pragma unroll
+  for (int g = 0; g < C::GR; ++g) {
+    const int dir = D == 3 ? wave + g * C::NWV : (lane / 8) & 1;
+    if (D == 3 ? (dir >= 3 || !((gmask >> (4 * dir)) & 15)) : (wave > 0 || !gmask)) continue;  // wave-uniform
+    const int d0 = dir == 0 ? 1 : 0, d1 = dir == 2 ? 1 : 2;
+    const int sd = dir == 0 ? 1 : dir == 1 ? W1 : W1 * W1;
+    const int s0 = d0 == 0 ? 1 : W1, s1 = D == 3 ? (d1 == 1 ? W1 : W1 * W1) : 0;
+    T y[NP1];
+#pragma unroll
+    for (int p = 0; p < NP1; ++p) y[p] = 0;
+    const T* xl = sm.xs + (K * t0 + (b0 < N1 ? b0 : 0)) * s0 + (K * t1 + (b1 < N1 ? b1 : 0)) * s1;
+    T xv[2 * K + 1];
+#pragma unroll
+    for (int q = 0; q <= 2 * K; ++q) xv[q] = xl[q * sd];
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+      const T* jm = sm.jg + m * W1;
+      const T* gj = sm.jg + (K + m) * W1;
+      T J0 = 0, J1 = 0, J2 = 0;
+#pragma unroll
+      for (int q = 0; q <= 2 * K; ++q) {
+        J0 += jm[q] * (q < K ? lo[g][q < K ? q : 0] : xv[q < K ? 0 : q - K]);
+        J1 += jm[q] * xv[q];
+        J2 += jm[q] * (q <= K ? xv[q <= K ? q + K : 0] : hi[g][q <= K ? 0 : q - K - 1]);
+      }
+      J0 = gf[g][0] ? J0 : (T)0;
+      J1 = gf[g][1] ? J1 : (T)0;
+      J2 = gf[g][2] ? J2 : (T)0;
+#pragma unroll
+      for (int p = 1; p < 2 * K; ++p) {
+        y[p - 1] += gj[p] * J1;
+        if (p <= K) y[p - 1] += gj[p <= K ? p + K : 0] * J0;
+        if (p >= K) y[p - 1] += gj[p >= K ? p - K : 0] * J2;
+      }
+    }
+    const int i0 = b0 - 1 + t0, i1 = b1 - 1 + t1;  // internal rows 0..k-1 of the tangential cell
+    const bool put = (D == 3 || tid < 16) && b0 < N1 && b1 < N1 && i0 >= 0 && i0 < K && (D == 2 || (i1 >= 0 && i1 < K));
+    T* h = sm.H[dir] + (D == 3 ? (t0 * K + i0) * 2 * K + t1 * K + i1 : t0 * K + i0);
+#pragma unroll
+    for (int p = 0; p < NP1; ++p) {
+      T s = w0[0] * lane_dpp<0x00>(y[p]) + w0[1] * lane_dpp<0x55>(y[p]);
+      if (N1 > 2) s += w0[2] * lane_dpp<0xaa>(y[p]);
+      if (N1 > 3) s += w0[3] * lane_dpp<0xff>(y[p]);
+      if (D == 3)
+        s = (w1[0] * s + w1[1] * lane_dpp<0x124>(s)) + (w1[2] * lane_dpp<0x128>(s) + w1[3] * lane_dpp<0x12c>(s));
+      if (put) h[p * C::HT] = s;
+    }
+  }
+  // cell rows: one partial sum per slab, the slabs in order
+#pragma unroll
+  for (int u = 0; u < C::NRND; ++u) {
+    const int t = tid + TH * u;
+    if (t >= C::NPAIR * C::PS) break;
+    int o, iloc;
+    pair_of(t / C::PS, o, iloc);
+    const T* xc = sm.xs + K * (o & 1) + W1 * K * ((o >> 1) & 1) + (D == 3 ? W1 * W1 * K * ((o >> 2) & 1) : 0);
+    if (C::PS > 1) xc += (t % C::PS) * (D == 3 ? W1 * W1 : W1);
+    const T* m = C::PRE ? nullptr : row_ptr(t);
+    T part = 0;
+#pragma unroll
+    for (int z = 0; z < C::SLABS / C::PS; ++z) {
+      T r[C::SL];
+#pragma unroll
+      for (int e = 0; e < C::SL; ++e) r[e] = C::PRE ? row[C::PRE ? u : 0][C::PRE ? z * C::SL + e : 0] : m[z * C::SL + e];
+      T s = 0;
+#pragma unroll
+      for (int e = 0; e < C::SL; ++e) s += r[e] * xc[e % N1 + W1 * (e / N1) + z * (D == 3 ? W1 * W1 : W1)];
+      part = z == 0 ? s : part + s;
+    }
+    sm.parts[t] = cell_fg(o) & 1 ? part : (T)0;
+  }
+  __syncthreads();
+  // residual rows
+  if (tid < nj) {
+    const int pi[3] = {pos % W1, (pos / W1) % W1, D == 3 ? pos / (W1 * W1) : 0};
+    // the node's pairs: per direction index j = p - 1 (layer 0, p <= k) and
+    // j = p (layer 1, p >= k); every choice is read, so that the reads are in
+    // flight together, and those that the node does not have are dropped
+    int jlo[3] = {0, 0, 0}, jn[3] = {1, 1, 1};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      jlo[a] = pi[a] <= K ? pi[a] - 1 : pi[a];
+      jn[a] = pi[a] == K ? 2 : 1;
+    }
+    T ax = 0;
+#pragma unroll
+    for (int e = 0; e < NCELL; ++e) {
+      int t = 0, st = 1;
+      bool has = true;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const int ea = (e >> a) & 1;
+        has = has && ea < jn[a];
+        t += (jlo[a] + (ea & (jn[a] - 1))) * st;
+        st *= 2 * K;
+      }
+      T p = sm.parts[t * C::PS];
+#pragma unroll
+      for (int z = 1; z < C::PS; ++z) p += sm.parts[t * C::PS + z];
+      ax += has ? p : (T)0;
+    }
+#pragma unroll
+    for (int dir = 0; dir < D; ++dir) {
+      constexpr int D1[3] = {2, 2, 1};
+      const int d0 = dir == 0 ? 1 : 0, d1 = D1[dir];
+#pragma unroll
+      for (int e = 0; e < NTC; ++e) {
+        const int e0 = e & 1, e1 = e >> 1;
+        const int j0 = jlo[d0] + (e0 & (jn[d0] - 1)), j1 = D == 3 ? jlo[d1] + (e1 & (jn[d1] - 1)) : 0;
+        const int t = (j0 >= K ? 1 : 0) | (j1 >= K ? 2 : 0);
+        const bool has = e0 < jn[d0] && (D == 2 || e1 < jn[d1]) && ((gmask >> (dir * NTC + t)) & 1);
+        const T h = sm.H[dir][(pi[dir] - 1) * C::HT + (D == 3 ? j0 * 2 * K + j1 : j0)];
+        ax += has ? h : (T)0;
+      }
+    }
+    sm.rs[tid] = bval - ax;
+  }
+  for (int e = nj + tid; e < C::RSN; e += TH) sm.rs[e] = 0;
+  __syncthreads();
+  // d = A_j^{-1} r: row i as column i (the inverse is symmetric), so that
+  // neighbouring rows read neighbouring entries; entry j goes to partial sum
+  // j % NACC.  Loads past the last entry re-read it (their residual is zero).
+  if (gi >= nj) return;
+  T dv;
+  T acc[C::NACC / C::GS];
+#pragma unroll
+  for (int u = 0; u < C::NACC / C::GS; ++u) acc[u] = 0;
+  if constexpr (C::SPLIT) {
+#pragma unroll
+    for (int e = 0; e < C::JP; ++e) acc[e % (C::NACC / C::GS)] += iv[e] * sm.rs[gu + C::GS * e];
+  } else {
+    constexpr int NB = NP <= 32 ? C::JP : (sizeof(T) == 4 ? 32 : 16);  // independent loads in flight
+    for (int j = 0; j < (NP <= 32 ? 1 : nj); j += NB) {
+      T r[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) r[u] = inv[(int64_t)(j + u < nj ? j + u : nj - 1) * nj];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) acc[u % C::NACC] += r[u] * sm.rs[j + u];
+    }
+  }
+  if constexpr (C::GS == 4) {
+    // lane u of the quad holds the partial sums u and (for 8) u + 4
+    T s[2];
+#pragma unroll
+    for (int u = 0; u < C::NACC / 4; ++u)
+      s[u] = (lane_dpp<0x00>(acc[u]) + lane_dpp<0x55>(acc[u])) + (lane_dpp<0xaa>(acc[u]) + lane_dpp<0xff>(acc[u]));
+    dv = C::NACC == 8 ? s[0] + s[C::NACC / 4 - 1] : s[0];
+  } else if constexpr (C::NACC == 8) {
+    dv = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  } else {
+    dv = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  }
+  if (gu != 0) return;
+  const int ps = sm.pos[gi];
   if (xb)
-    xb[node] = xold + dv;
+    xb[cbase + loff(ps)] = sm.xs[ps] + dv;
   else
-    dbuf[off + tid] = dv;
+    dbuf[off + gi] = dv;
 }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -1756,18 +1599,6 @@ struct ColsSmem {
   int16_t pos[C::NPP];
 };
 
-// The value that the DPP pattern CTRL brings to this lane: 0x55 q the lane q of
-// its quad, 0x120 + n the lane n below it in its row of 16 (cyclic).
-template <int CTRL>
-__device__ __forceinline__ float lane_dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_dpp(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
-}
-
 template <int D, int K, typename T, int NW>
 __device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev& G, const T* __restrict__ x,
                                               const T* __restrict__ b, T* __restrict__ dbuf, T* __restrict__ xb,
@@ -1804,10 +1635,9 @@ __device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev
   const int64_t nn = L.nn, nn2 = nn * nn;
   int V[3] = {0, 0, 0};
   {
-    int vr = G.vertex[gp];
-    const int NV = L.N + 1;
+    const uint64_t vp = G.vpack[gp];
 #pragma unroll
-    for (int a = 0; a < D; ++a) { V[a] = vr % NV; vr /= NV; }
+    for (int a = 0; a < D; ++a) V[a] = static_cast<int>(vp >> (21 * a)) & 0x1fffff;
   }
   const int64_t cbase = K * (V[0] - 1) + nn * (K * (V[1] - 1)) + (D == 3 ? nn2 * (K * (V[2] - 1)) : 0);
   // local index of row r (of the k^d internal rows of cell o), and its pair index
@@ -1875,11 +1705,10 @@ __device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev
   // first cell only where all of them would take more than 64 registers)
   constexpr int NCW = NCELL / NW;
   constexpr bool ALL = NCW * C::NRT * NKS * (int)sizeof(T) <= 64 * 4;
-  uint64_t fgq[NCELL / 4];  // flags of the 2^d cells, 4 cells a word (scalar loads)
-#pragma unroll
-  for (int i = 0; i < NCELL / 4; ++i)
-    fgq[i] = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4) + i];
-  auto cell_fg = [&](int o) { return static_cast<int>(((NCELL > 4 && o >= 4) ? fgq[NCELL / 4 - 1] : fgq[0]) >> (16 * (o & 3))) & 0xffff; };
+  // flags of the 2^d cells, 4 cells a word
+  const uint64_t fga = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4)];
+  const uint64_t fgb = reinterpret_cast<const uint64_t*>(G.cell_fg)[(int64_t)gp * (NCELL / 4) + NCELL / 4 - 1];
+  auto cell_fg = [fga, fgb](int o) { return static_cast<int>((o >= 4 ? fgb : fga) >> (16 * (o & 3))) & 0xffff; };
   int fg[NCW], cut[NCW];
   T am[ALL ? NCW : 1][C::NRT][NKS];
 #pragma unroll
@@ -1921,35 +1750,29 @@ __device__ __forceinline__ void cut_cols_body(const KLevel& L, const CutGroupDev
     for (int e = NC * ncol + tid; e < NC * kMaxCols; e += TH) (&sm.xs[0][0])[e] = 0;
   }
   // level tables: mass, jump weights j_m(s) and gc_m j_m(s)
-  for (int t = tid; t < N1 * N1; t += TH) (&sm.mh[0][0])[t] = (T)L.tables[S::T_MHAT + t];
-  for (int t = tid; t < K * (2 * K + 1); t += TH) {
-    const int m = t / (2 * K + 1), s = t % (2 * K + 1);
-    double j = 0.0;
-    if (s <= K) j += L.tables[S::T_D1 + m * N1 + s];
-    if (s >= K) j -= L.tables[S::T_D0 + m * N1 + (s - K)];
-    sm.jm[m][s] = (T)j;
-    sm.gj[m][s] = (T)(L.tables[S::T_GC + m] * j);
+  for (int t = tid; t < N1 * N1; t += TH) (&sm.mh[0][0])[t] = L.tables_t<T>()[S::T_MHAT + t];
+  for (int t = tid; t < K * W1; t += TH) {
+    (&sm.jm[0][0])[t] = L.tables_t<T>()[S::T_JM + t];
+    (&sm.gj[0][0])[t] = L.tables_t<T>()[S::T_GJ + t];
   }
   // (node, column) task of the thread: row ti, columns tc + CPI u
   const int ti = tid % C::NPT, tc = tid / C::NPT;
   int pi[3] = {0, 0, 0};
   T bv[C::NRD];
   if (ti < nj) {
-    const int node = G.nodes[off + ti];
+    const int ps = G.pos[off + ti];
+    pi[0] = ps % W1;
+    pi[1] = (ps / W1) % W1;
+    pi[2] = D == 3 ? ps / (W1 * W1) : 0;
+    const int node = static_cast<int>(cbase + pi[0] + nn * pi[1] + (D == 3 ? nn2 * pi[2] : 0));
 #pragma unroll
     for (int u = 0; u < C::NRD; ++u) {
       const int c = tc + C::CPI * u;
       bv[u] = c < ncol ? b[c * L.n_nodes + node] : (T)0;
     }
-    int r = node;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      pi[a] = r % L.nn - K * (V[a] - 1);
-      r /= L.nn;
-    }
     if (tc == 0) {
       sm.node[ti] = node;
-      sm.pos[ti] = static_cast<int16_t>(pi[0] + W1 * pi[1] + (D == 3 ? W1 * W1 * pi[2] : 0));
+      sm.pos[ti] = static_cast<int16_t>(ps);
     }
   }
   __syncthreads();
@@ -2701,21 +2524,26 @@ hipError_t launch_cut_solve(int d, int k, const KLevel& L, const CutGroupDev& G,
   if (G.n_patch == 0) return hipSuccess;
   if (record_none()) return hipSuccess;
   return dispatch(d, k, [&](auto D, auto K) {
-    using C = dev::CutShape<D.value, K.value>;
     if (xb == nullptr && cj.n != 0) return hipErrorInvalidValue;  // a copy job needs the second buffer
     // small launches (the coarse levels) are bound by the latency of one patch
-    // block: twice the threads per patch shortens its serial passes; large
-    // ones keep the smaller blocks for occupancy
+    // block: more threads per patch shorten its serial passes; large ones keep
+    // the smaller blocks for occupancy
     auto go = [&](auto th) {
       constexpr int TH = decltype(th)::value;
+      using C = dev::CutShape<D.value, K.value, T, TH>;
       CopyJob c2 = cj;
       c2.nblk = static_cast<int>((cj.n + TH * C::COPY - 1) / (TH * C::COPY));
       hipLaunchKernelGGL((dev::k_cut_solve<D.value, K.value, T, TH>), dim3(c2.nblk + G.n_patch, ncol), dim3(TH), 0,
                          s, L, G, x, b, dbuf, xb, c2);
       return hipGetLastError();
     };
-    if (C::THREADS < 256 && G.n_patch < lp.small_cut_launch) return go(std::integral_constant<int, 2 * C::THREADS>{});
-    return go(std::integral_constant<int, C::THREADS>{});
+    constexpr int TL = dev::CutThreads<D.value, K.value>::v;
+    // small launches: Q1 patches (one node) have nothing to split; a 512-thread
+    // block takes most of a CU's registers, so Q3 turns to it later
+    constexpr int TS = K.value == 1 ? TL : D.value == 2 ? 128 : K.value == 3 ? 512 : 256;
+    if (G.n_patch * (TS == 512 ? int64_t{4} : int64_t{1}) < lp.small_cut_launch)
+      return go(std::integral_constant<int, TS>{});
+    return go(std::integral_constant<int, TL>{});
   });
 }
 
