@@ -2150,98 +2150,138 @@ struct ProlongAddArgs {
   __device__ void run() const { prolong_add_body<D, K, T>(Lc, Lf, xc, xf); }
 };
 
-// b_c[J] = sum_I P(I, J) r_f[I] for every active coarse node (transpose).  In
-// every direction the fine nodes with a non-zero weight form one contiguous
-// range: [2J-2k+1, 2J+2k-1] around a coarse vertex, [2kC+1, 2kC+2k-1] inside a
-// coarse cell C; the weights are read from the 1-D prolongation table.
-template <int K>
-__device__ __forceinline__ double restrict_weight(const double* p1d, int J, int I) {
-  constexpr int N1 = K + 1;
-  if (J % K == 0) {
-    const int v = J / K;
-    if (I == 2 * J) return 1.0;
-    if (I < 2 * J) return p1d[(I - 2 * K * (v - 1)) * N1 + K];
-    return p1d[(I - 2 * K * v) * N1 + 0];
-  }
-  const int C = J / K;
-  return p1d[(I - 2 * K * C) * N1 + J % K];
-}
-
-template <int D, int K, typename T>
-__device__ __forceinline__ void restrict_body(KLevel Lc, KLevel Lf, const T* __restrict__ rf, T* __restrict__ bc) {
+// Coarse cells per direction of one restriction block.
+template <int D, int K>
+struct RestrictShape {
   using S = Shape<D, K>;
-  constexpr int N1 = S::N1;
-  __shared__ double p1d[S::NC1 * N1];
-  for (int t = threadIdx.x; t < S::NC1 * N1; t += blockDim.x) p1d[t] = Lf.tables[S::T_P1D + t];
-  __syncthreads();
+  static constexpr int TB = ApplyShape<D, K>::B;                  // cells of an operator tile (whose lists are used)
+  static constexpr int RB = D == 3 && K > 1 ? 2 : TB;             // cells of a block
+  static constexpr int SUB = TB / RB;                             // blocks per tile and direction
+  static constexpr int NSUB = Pow<SUB, D>::v;
+  static constexpr int O1 = RB * K + 1;                           // owned coarse nodes (last tile: + 1)
+  static constexpr int S1 = 2 * K * RB + 2 * K;                   // staged fine nodes
+  static constexpr int NT = 4 * K - 1;                            // fine nodes below a coarse vertex node
+};
+
+// b_c[J] = sum_I P(I, J) r_f[I] on the coarse nodes of a block of RB^d coarse
+// cells (transpose of the embedding), by one 1-D pass per direction in LDS: P is
+// a tensor product, and in every direction the fine nodes with a non-zero weight
+// form one range, [2J-2k+1, 2J+2k-1] around a coarse vertex node and [2kC+1,
+// 2kC+2k-1] inside a coarse cell C.  The blocks are the coarse level's operator
+// tiles (those owning active nodes) cut into RB^d cells; fine nodes beyond the
+// box count as zero, and coarse nodes that are not active receive the sum of
+// the zeros around them.  A block stages its fine nodes with all loads in
+// flight; a wave works on rows of one coarse node, so it is bound by a short
+// chain where one thread per node made (4k-1)^d steps.  128^3 ball, Q2, FP64: 77.8
+// -> 38.6 us on the finest level, 24.6 -> 9.8 us at 32^3 cells; Q3 union at 32^3 94.5
+// -> 15.1 us; circle, Q3, 1024^2, 76.1 -> 31.5 us.
+template <int D, int K, typename T>
+__device__ __forceinline__ void restrict_body(const KLevel& Lc, const KLevel& Lf, const T* __restrict__ rf,
+                                              T* __restrict__ bc) {
+  using S = Shape<D, K>;
+  using R = RestrictShape<D, K>;
+  constexpr int N1 = S::N1, S1 = R::S1, O1 = R::O1, NT = R::NT;
+  constexpr int NF = Pow<S1, D>::v;       // fine nodes
+  constexpr int P1 = S1 | 1;              // line stride in LDS, odd
+  constexpr int NL0 = NF / S1;            // lines along direction 0
+  constexpr int NG = D == 3 ? S1 * P1 : P1;  // first-pass values per coarse node
+  constexpr int NA = NG * O1, NB = D == 3 ? P1 * O1 * O1 : 1;
+  __shared__ T f[NL0 * P1 > NB ? NL0 * P1 : NB];  // fine nodes; in 3-D then the second pass
+  __shared__ T g[NA];                 // first pass
+  __shared__ T w[K][NT];              // weights: 0 the vertex node, i the i-th node inside a cell
+  const int ntile = Lc.n_tiles + Lc.n_tiles_sf;
+  const int ti = blockIdx.x / R::NSUB;
+  if (ti >= ntile) return;  // grouped launches: a block beyond this problem's tiles
   rf += blockIdx.y * Lf.n_nodes;  // column blockIdx.y
   bc += blockIdx.y * Lc.n_nodes;
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= Lc.n_dofs) return;
-  const int32_t node = Lc.dof_node[j];
-  int J[3], lo[3], hi[3];
-  int r = node;
+  for (int t = threadIdx.x; t < K * NT; t += 256) {
+    const int i = t / NT, e = t % NT;
+    int at = -1;  // entry of the 1-D prolongation table
+    if (i == 0) at = e < 2 * K - 1 ? (e + 1) * N1 + K : e > 2 * K - 1 ? (e - (2 * K - 1)) * N1 : -1;
+    else if (e < 2 * K - 1) at = (e + 1) * N1 + i;
+    w[i][e] = at >= 0 ? (T)Lf.tables[S::T_P1D + at] : i == 0 ? (T)1 : (T)0;
+  }
+  int c0[3] = {0, 0, 0};  // first coarse node of the block
+  {
+    const int NTd = (Lc.N + R::TB - 1) / R::TB;
+    int r = ti < Lc.n_tiles ? Lc.tiles[ti] : Lc.tiles_sf[ti - Lc.n_tiles], q = blockIdx.x % R::NSUB;
 #pragma unroll
-  for (int a = 0; a < D; ++a) {
-    J[a] = r % Lc.nn;
-    r /= Lc.nn;
-    if (J[a] % K == 0) {
-      lo[a] = 2 * J[a] - 2 * K + 1;
-      hi[a] = 2 * J[a] + 2 * K - 1;
+    for (int a = 0; a < D; ++a) {
+      c0[a] = K * (R::TB * (r % NTd) + R::RB * (q % R::SUB));
+      r /= NTd;
+      q /= R::SUB;
+    }
+  }
+  const int nf = Lf.nn;
+  {
+    constexpr int NIT = (NF + 255) / 256, UB = NIT < 12 ? NIT : 12;
+    for (int u0 = 0; u0 < NIT; u0 += UB) {
+      T v[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int e = threadIdx.x + 256 * (u0 + u);
+        int I[3], r = e;
+        bool in = e < NF;
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          I[a] = 2 * c0[a] - (2 * K - 1) + r % S1;
+          r /= S1;
+          in = in && I[a] >= 0 && I[a] < nf;
+        }
+        v[u] = in ? rf[lat(D, nf, I)] : (T)0;
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int e = threadIdx.x + 256 * (u0 + u);
+        if (e < NF) f[(e / S1) * P1 + e % S1] = v[u];
+      }
+    }
+  }
+  __syncthreads();
+  // sum over the fine range of coarse node q on one line; the range of the last
+  // node ends with the box (or the node belongs to the next block)
+  auto line = [&](const T* s, int q) {
+    T acc = 0;
+    if (q % K == 0) {
+#pragma unroll
+      for (int e = 0; e < NT; ++e)
+        if (e < 2 * K || q < R::RB * K) acc += w[0][e] * s[2 * q + e];
     } else {
-      const int C = J[a] / K;
-      lo[a] = 2 * K * C + 1;
-      hi[a] = 2 * K * C + 2 * K - 1;
+#pragma unroll
+      for (int e = 0; e < 2 * K - 1; ++e) acc += w[q % K][e] * s[2 * K * (q / K) + 2 * K + e];
     }
-    lo[a] = lo[a] < 0 ? 0 : lo[a];
-    hi[a] = hi[a] > Lf.nn - 1 ? Lf.nn - 1 : hi[a];
+    return acc;
+  };
+  // direction 0: g[q0][direction 2][direction 1]
+  for (int t = threadIdx.x; t < NL0 * O1; t += 256) {
+    const int q0 = t / NL0, r = t % NL0;
+    g[q0 * NG + (D == 3 ? (r / S1) * P1 + r % S1 : r)] = line(f + r * P1, q0);
   }
-  // 1-D weights over the (at most 4k-1 wide) ranges, zero beyond them; the
-  // loads of one x-y slab are issued together
-  constexpr int WR = 4 * K - 1;
-  T w[2][WR];  // directions 0 and 1; direction 2 inside the slab loop (a runtime index)
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int t = 0; t < WR; ++t) w[a][t] = lo[a] + t <= hi[a] ? (T)restrict_weight<K>(p1d, J[a], lo[a] + t) : (T)0;
-  const int64_t nn = Lf.nn;
-  T acc = 0;
-  for (int t2 = 0; t2 < (D == 3 ? WR : 1); ++t2) {
-    if (D == 3 && lo[2] + t2 > hi[2]) break;
-    const int64_t base = lo[0] + nn * (lo[1] + (D == 3 ? nn * (lo[2] + t2) : 0));
-    T a1 = 0;
-    if constexpr (WR * WR * sizeof(T) <= 400) {  // the slab fits in about 100 registers
-      T v[WR][WR];
-#pragma unroll
-      for (int t1 = 0; t1 < WR; ++t1)
-#pragma unroll
-        for (int t0 = 0; t0 < WR; ++t0)
-          v[t1][t0] = (lo[1] + t1 <= hi[1] && lo[0] + t0 <= hi[0]) ? rf[base + t0 + nn * t1] : (T)0;
-#pragma unroll
-      for (int t1 = 0; t1 < WR; ++t1) {
-        if (lo[1] + t1 > hi[1]) continue;
-        T a0 = 0;
-#pragma unroll
-        for (int t0 = 0; t0 < WR; ++t0)
-          if (lo[0] + t0 <= hi[0]) a0 += w[0][t0] * v[t1][t0];
-        a1 += w[1][t1] * a0;
-      }
-    } else {  // row by row
-      for (int t1 = 0; t1 < WR; ++t1) {
-        if (lo[1] + t1 > hi[1]) break;
-        T v[WR];
-#pragma unroll
-        for (int t0 = 0; t0 < WR; ++t0) v[t0] = lo[0] + t0 <= hi[0] ? rf[base + t0 + nn * t1] : (T)0;
-        T a0 = 0;
-#pragma unroll
-        for (int t0 = 0; t0 < WR; ++t0)
-          if (lo[0] + t0 <= hi[0]) a0 += w[0][t0] * v[t0];
-        a1 += (T)restrict_weight<K>(p1d, J[1], lo[1] + t1) * a0;
-      }
+  __syncthreads();
+  if constexpr (D == 3) {
+    // direction 1: f[q1][q0][direction 2]
+    for (int t = threadIdx.x; t < S1 * O1 * O1; t += 256) {
+      const int s2 = t % S1, q0 = (t / S1) % O1, q1 = t / (S1 * O1);
+      f[(q1 * O1 + q0) * P1 + s2] = line(g + q0 * NG + s2 * P1, q1);
     }
-    acc += D == 3 ? (T)restrict_weight<K>(p1d, J[2], lo[2] + t2) * a1 : a1;
+    __syncthreads();
   }
-  bc[node] = acc;
+  // last direction, at every owned coarse node
+  constexpr int NO = Pow<O1, D>::v;
+  for (int t = threadIdx.x; t < NO; t += 256) {
+    int q[3], J[3], r = t;
+    bool own = true;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      q[a] = r % O1;
+      r /= O1;
+      J[a] = c0[a] + q[a];
+      // the last layer belongs to the next block unless the box ends here
+      own = own && J[a] < Lc.nn && (q[a] < R::RB * K || J[a] == Lc.nn - 1);
+    }
+    if (!own) continue;
+    bc[lat(D, Lc.nn, J)] = D == 3 ? line(f + (q[1] * O1 + q[0]) * P1, q[2]) : line(g + q[0] * NG, q[1]);
+  }
 }
 
 template <int D, int K, typename T>
@@ -2630,10 +2670,9 @@ template <typename T>
 hipError_t launch_restrict(int d, int k, const KLevel& Lc, const KLevel& Lf, const T* rf, T* bc, hipStream_t s,
                            int ncol) {
   return dispatch(d, k, [&](auto D, auto K) {
-    if (record<256>(dim3(blocks(Lc.n_dofs), ncol), dim3(256), dev::RestrictArgs<D.value, K.value, T>{Lc, Lf, rf, bc}))
-      return hipSuccess;
-    hipLaunchKernelGGL((dev::k_restrict<D.value, K.value, T>), dim3(blocks(Lc.n_dofs), ncol), dim3(256), 0, s, Lc,
-                       Lf, rf, bc);
+    const dim3 g(std::max(1, Lc.n_tiles + Lc.n_tiles_sf) * dev::RestrictShape<D.value, K.value>::NSUB, ncol);
+    if (record<256>(g, dim3(256), dev::RestrictArgs<D.value, K.value, T>{Lc, Lf, rf, bc})) return hipSuccess;
+    hipLaunchKernelGGL((dev::k_restrict<D.value, K.value, T>), g, dim3(256), 0, s, Lc, Lf, rf, bc);
     return hipGetLastError();
   });
 }
