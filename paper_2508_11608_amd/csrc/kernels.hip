@@ -563,17 +563,6 @@ __device__ __forceinline__ double tile1d(const double* e, int s, int j) {
     if (s >= K * c && s <= K * c + K && j >= K * c && j <= K * c + K) v += e[(s - K * c) * (K + 1) + (j - K * c)];
   return v;
 }
-// The same for a run-time row s: the cells holding s are s/K - 1 and s/K when
-// s is a cell boundary, else s/K.
-template <int K, int NCELL>
-__device__ __forceinline__ double tile1d_rt(const double* e, int s, int j) {
-  const int c1 = s / K, c0 = s % K == 0 ? c1 - 1 : c1;
-  double v = 0;
-  for (int c = c0; c <= c1; ++c)
-    if (c >= 0 && c < NCELL && j >= K * c && j <= K * c + K) v += e[(s - K * c) * (K + 1) + (j - K * c)];
-  return v;
-}
-
 // A run-time row s >= K of the assembled 1-D matrices of a tile: 2k+1 taps from
 // column first on, the last k of them step apart.  A cell boundary couples
 // with both its cells (step 1); any other node, and the line's last one, only
@@ -585,13 +574,19 @@ struct TileRow {
   T m[2 * K + 1], k[2 * K + 1];
   __device__ __forceinline__ void load(const double* em, const double* ek, int s) {
     const bool wide = s % K == 0 && s < NCELL * K;
-    first = wide ? s - K : s == NCELL * K ? s - K : K * (s / K);
+    const int i = wide || s == NCELL * K ? K : s % K;  // row of the (lower) cell's element matrix
+    first = s - i;
     step = wide ? 1 : 0;
 #pragma unroll
     for (int t = 0; t <= 2 * K; ++t) {
-      const bool has = wide || t <= K;
-      m[t] = has ? (T)tile1d_rt<K, NCELL>(em, s, first + t) : (T)0;
-      k[t] = has ? (T)tile1d_rt<K, NCELL>(ek, s, first + t) : (T)0;
+      T vm = t <= K ? (T)em[i * (K + 1) + (t <= K ? t : 0)] : (T)0, vk = t <= K ? (T)ek[i * (K + 1) + (t <= K ? t : 0)] : (T)0;
+      if (t >= K) {  // the upper cell's first row
+        const double um = em[t >= K ? t - K : 0], uk = ek[t >= K ? t - K : 0];
+        vm = wide ? (T)((t == K ? em[i * (K + 1) + K] : 0.0) + um) : vm;
+        vk = wide ? (T)((t == K ? ek[i * (K + 1) + K] : 0.0) + uk) : vk;
+      }
+      m[t] = vm;
+      k[t] = vk;
     }
   }
   __device__ __forceinline__ int at(int t) const { return first + (t <= K ? t : K + (t - K) * step); }
@@ -612,7 +607,7 @@ struct TileRow {
 // its registers; a block works on as many tiles at once as its threads cover,
 // and the next tiles' x is on its way while the current ones are contracted.
 // The former form gave the first pass one thread per line, 16 of 256 for Q3.
-// Circle, Q3, 1024^2 cells (6.1 million DoFs), FP64: 298 -> 95 us; now bound by
+// Circle, Q3, 1024^2 cells (6.1 million DoFs), FP64: 298 -> 75 us; now bound by
 // the 22 LDS reads of a node (one 8-byte word a clock and bank pair).
 template <int K, typename T>
 __device__ __forceinline__ void apply_sf2_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
@@ -630,9 +625,16 @@ __device__ __forceinline__ void apply_sf2_body(const KLevel& L, const T* __restr
   const int p = threadIdx.x / NR, r = threadIdx.x % NR;
   const int i0 = r % R1, i1 = r / R1;  // staged node, and (line, row) of the first pass
   const int q0 = r % O1, q1 = r / O1;  // owned node
+  constexpr int NE = S::N1 * S::N1;
+  __shared__ double em[NE], ek[NE];  // element mass and stiffness: one load, then the rows out of LDS
+  for (int i = threadIdx.x; i < NE; i += 256) {
+    em[i] = L.tables[S::T_MHAT + i];
+    ek[i] = L.tables[S::T_K1S + i];
+  }
+  __syncthreads();
   TileRow<K, C1, T> r1, r0;
-  r1.load(L.tables + S::T_MHAT, L.tables + S::T_K1S, K + (i1 < O1 ? i1 : 0));
-  r0.load(L.tables + S::T_MHAT, L.tables + S::T_K1S, K + q0);
+  r1.load(em, ek, K + (i1 < O1 ? i1 : 0));
+  r0.load(em, ek, K + q0);
   const int step = gridDim.x * TP;
   auto load = [&](int ti, int& tile) {
     tile = p < TP && ti < L.n_tiles_sf ? L.tiles_sf[ti] : -1;
@@ -691,11 +693,21 @@ __device__ __forceinline__ void apply_sf3_body(const KLevel& L, const T* __restr
   constexpr int NXV = A::NR > 2 * NW ? A::NR : 2 * NW;
   constexpr int NU = R1 * R1 * O1;                       // values per first-pass array
   __shared__ T xv[NXV];     // x staged, then the second pass: [0, NW) and [NW, 2 NW)
-  __shared__ T ua[2][NU];   // first pass: Mhat x and Khat x along the slowest direction
+  __shared__ __align__(16) T ua[2][NU];  // first pass: Mhat x and Khat x along the slowest direction
   __shared__ TileRow<K, C1, T> rows[O1];
   const double* m1 = L.tables + S::T_MHAT;
   const double* k1 = L.tables + S::T_K1S;
-  if (threadIdx.x < O1) rows[threadIdx.x].load(m1, k1, K + threadIdx.x);
+  {
+    constexpr int NE = S::N1 * S::N1;
+    double* e = reinterpret_cast<double*>(&ua[0][0]);  // free until the first tile's first pass
+    static_assert(sizeof(ua) >= 2 * NE * sizeof(double), "the element matrices fit");
+    for (int i = threadIdx.x; i < NE; i += 256) {
+      e[i] = m1[i];
+      e[NE + i] = k1[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < O1) rows[threadIdx.x].load(e, e + NE, K + threadIdx.x);
+  }
   x += blockIdx.y * L.n_nodes;  // column blockIdx.y
   if (b) b += blockIdx.y * L.n_nodes;
   y += blockIdx.y * L.n_nodes;
