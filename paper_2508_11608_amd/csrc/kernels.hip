@@ -112,6 +112,30 @@ __device__ void load_tables(const double* __restrict__ g, double* s, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) s[i] = g[i];
 }
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// One 16x16x4 matrix-core product: lane l holds A(l%16, l/16) and B(l/16,
+// l%16); of D it holds column l%16 and, as element v, row mfma_row(l, v).
+__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ doublex4 mfma16(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  using Acc = floatx4;
+  static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane / 16) + v; }
+};
+template <>
+struct Mfma<double> {
+  using Acc = doublex4;
+  static __device__ __forceinline__ int row(int lane, int v) { return 4 * v + lane / 16; }
+};
+
 // Ghost-face pre-pass of the operator: for every ghost face and derivative order
 // m, the jump J_m(b_t) = sum_bd psi_bd^(m)(1) x_lower - psi_bd^(m)(0) x_upper at the
 // tangential face nodes b_t, contracted with the reference face mass:
@@ -389,8 +413,8 @@ struct ApplyShape {
 // (from LDS) or the special-cell value of the pre-pass (from C).  The C loads
 // of a node's cells are independent and issued together before the LDS rows.
 template <int D, int K, typename T>
-__device__ __forceinline__ void apply_body(KLevel L, const T* __restrict__ x, const T* __restrict__ b,
-                                           T* __restrict__ y, const T* __restrict__ C) {
+__device__ __forceinline__ void apply_rows_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                                T* __restrict__ y, const T* __restrict__ C) {
   using S = Shape<D, K>;
   using A = ApplyShape<D, K>;
   constexpr int N1 = S::N1, NL = S::NL, B = A::B, R1 = A::R1, C1 = A::C1, O1 = A::O1;
@@ -526,6 +550,173 @@ __device__ __forceinline__ void apply_body(KLevel L, const T* __restrict__ x, co
       y[node] = b ? bv - ax : ax;
     }
   }
+}
+
+// The same for Q2 and Q3 in 3-D, the regular cells on the matrix cores: they all
+// have one stiffness matrix, so the products of 16 cells are 16x16x4 products
+// of its rows (kept in a wave's registers for all tiles of the block) with the
+// cells' x as columns, left in LDS as one value per cell and node; every owned
+// node then sums its up to 2^d cells' values (from LDS, or the pre-pass's from
+// C) with all reads in flight.  Dense rows node by node made every wave walk
+// 8 (k+1)^3 terms for the few nodes that lie in 8 cells, at two LDS reads a
+// term.  128^3 ball, Q2, FP64: product 229 -> 181 us; ball at 32^3 51 -> 38 us; Q3
+// union at 32^3, residual of 8 columns 314 -> 232 us.
+template <int K, typename T>
+__device__ __forceinline__ void apply_mfma_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                                T* __restrict__ y, const T* __restrict__ C) {
+  using S = Shape<3, K>;
+  using A = ApplyShape<3, K>;
+  using Acc = typename Mfma<T>::Acc;
+  constexpr int N1 = S::N1, NL = S::NL, B = A::B, R1 = A::R1, C1 = A::C1, O1 = A::O1, NCC = A::NCC;
+  constexpr int NRT = (NL + 15) / 16, NKS = (NL + 3) / 4, YS = NL | 1;
+  static_assert(4 % NRT == 0 && NCC <= 128, "row tiles per wave, cells per block");
+  __shared__ T xs[A::NR];
+  __shared__ T Y[NCC][YS];        // cell products of the regular cells, in list order
+  __shared__ int32_t csid[NCC];   // special id; the cells of the list: -3 - place in it
+  __shared__ int16_t list[NCC];   // first staged node of every regular cell
+  __shared__ int nreg;
+  const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int lr = lane % 16, lk = lane / 16, rt = wave % NRT;
+  T a[NKS];  // rows 16 rt .. of the uncut stiffness
+  {
+    const int r = rt * 16 + lr;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      const int q = 4 * ks + lk;
+      const T e = L.kcell_t<T>()[S::T_KCELL + (r < NL ? r : 0) * NL + (q < NL ? q : 0)];
+      a[ks] = r < NL && q < NL ? e : (T)0;
+    }
+  }
+  x += blockIdx.y * L.n_nodes;  // column blockIdx.y
+  if (b) b += blockIdx.y * L.n_nodes;
+  y += blockIdx.y * L.n_nodes;
+  C += blockIdx.y * L.n_spec * NL;
+  const int NTd = (L.N + B - 1) / B;
+  for (int ti = blockIdx.x; ti < L.n_tiles; ti += gridDim.x) {
+    __syncthreads();
+    const int tile = L.tiles[ti];
+    const int tc[3] = {tile % NTd, (tile / NTd) % NTd, tile / (NTd * NTd)};
+    {
+      constexpr int NIT = (A::NR + 255) / 256;
+      T v[NIT];
+#pragma unroll
+      for (int u = 0; u < NIT; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        int I[3], r = e;
+        bool in = e < A::NR;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          I[d] = K * (B * tc[d] - 1) + r % R1;
+          r /= R1;
+          in = in && I[d] >= 0 && I[d] < L.nn;
+        }
+        v[u] = in ? x[lat(3, L.nn, I)] : (T)0;
+      }
+      if (wave == 0) {
+        // the cells' special ids, and the list of the regular ones in cell order
+        int n = 0;
+#pragma unroll
+        for (int h = 0; h < (NCC + 63) / 64; ++h) {
+          const int e = lane + 64 * h;
+          int c[3], r = e;
+          bool in = e < NCC;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            c[d] = B * tc[d] - 1 + r % C1;
+            r /= C1;
+            in = in && c[d] >= 0 && c[d] < L.N;
+          }
+          const int sid = in ? L.cell_sid[cell_lin(3, L.N, c)] : -2;
+          const uint64_t m = __ballot(sid == -1);
+          const int at = n + __popcll(m & ((1ull << lane) - 1));
+          if (e < NCC) csid[e] = sid == -1 ? -3 - at : sid;
+          if (sid == -1) list[at] = static_cast<int16_t>(K * (e % C1 + R1 * ((e / C1) % C1 + R1 * (e / (C1 * C1)))));
+          n += __popcll(m);
+        }
+        if (lane == 0) nreg = n;
+      }
+#pragma unroll
+      for (int u = 0; u < NIT; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        if (e < A::NR) xs[e] = v[u];
+      }
+    }
+    __syncthreads();
+    const int nr = nreg;
+    for (int g = wave / NRT; g * 16 < nr; g += 4 / NRT) {  // wave-uniform: every lane takes part in the products
+      const int slot = g * 16 + lr;
+      const T* xc = xs + list[slot < nr ? slot : 0];
+      Acc acc = {0, 0, 0, 0};
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        const int q = 4 * ks + lk;
+        const int at = q % N1 + R1 * ((q / N1) % N1 + R1 * (q / (N1 * N1)));
+        acc = mfma16(a[ks], q < NL ? xc[at] : (T)0, acc);
+      }
+      if (slot < nr) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = rt * 16 + Mfma<T>::row(lane, v);
+          if (r < NL) Y[slot][r] = acc[v];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int e = threadIdx.x; e < A::NO; e += 256) {
+      const int q[3] = {e % O1, (e / O1) % O1, e / (O1 * O1)};
+      bool own = true;
+      int I[3];
+      // the node's cells along each direction: a node on a cell boundary lies in
+      // the staged cells q/K (local index K) and q/K + 1 (0), any other in q/K + 1
+      int cc[3][2], il[3][2], two[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        I[d] = K * B * tc[d] + q[d];
+        // the layer q = B K belongs to the next tile unless this is the last one
+        own = own && I[d] < L.nn && (q[d] < B * K || tc[d] == NTd - 1);
+        const bool edge = q[d] % K == 0;
+        cc[d][0] = edge ? q[d] / K : q[d] / K + 1;
+        il[d][0] = edge ? K : q[d] % K;
+        two[d] = edge && q[d] / K + 1 < C1;  // (not beyond the background box)
+        cc[d][1] = two[d] ? q[d] / K + 1 : cc[d][0];
+        il[d][1] = two[d] ? 0 : il[d][0];
+      }
+      if (!own) continue;
+      const int64_t node = lat(3, L.nn, I);
+      const T bv = b ? b[node] : (T)0;
+      T cv[8], yv[8];
+      bool act = false;  // the node lies in an active cell
+#pragma unroll
+      for (int comb = 0; comb < 8; ++comb) {
+        const int s0 = comb & 1, s1 = (comb >> 1) & 1, s2 = comb >> 2;
+        const bool has = (!s0 || two[0]) && (!s1 || two[1]) && (!s2 || two[2]);
+        const int sid = csid[cc[0][s0] + C1 * (cc[1][s1] + C1 * cc[2][s2])];
+        const int iloc = il[0][s0] + N1 * (il[1][s1] + N1 * il[2][s2]);
+        act = act || (has && sid != -2);
+        cv[comb] = has && sid >= 0 ? C[(int64_t)sid * NL + iloc] : (T)0;
+        const T r = Y[sid <= -3 ? -3 - sid : 0][iloc];
+        yv[comb] = has && sid <= -3 ? r : (T)0;
+      }
+      if (!act) continue;
+      T ax = 0;
+#pragma unroll
+      for (int comb = 0; comb < 8; ++comb) ax += yv[comb];
+#pragma unroll
+      for (int comb = 0; comb < 8; ++comb) ax += cv[comb];
+      y[node] = b ? bv - ax : ax;
+    }
+  }
+}
+
+template <int D, int K, typename T>
+__device__ __forceinline__ void apply_body(const KLevel& L, const T* __restrict__ x, const T* __restrict__ b,
+                                           T* __restrict__ y, const T* __restrict__ C) {
+  // Q1 rows have 8 entries, too few for a row tile, and 2-D meshes few mixed tiles
+  if constexpr (D == 3 && K > 1)
+    apply_mfma_body<K, T>(L, x, b, y, C);
+  else
+    apply_rows_body<D, K, T>(L, x, b, y, C);
 }
 
 template <int D, int K, typename T>
@@ -1516,30 +1707,6 @@ __global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G, const
   else
     dbuf[off + gi] = dv;
 }
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-// One 16x16x4 matrix-core product: lane l holds A(l%16, l/16) and B(l/16,
-// l%16); of D it holds column l%16 and, as element v, row mfma_row(l, v).
-__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ doublex4 mfma16(double a, double b, doublex4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<float> {
-  using Acc = floatx4;
-  static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane / 16) + v; }
-};
-template <>
-struct Mfma<double> {
-  using Acc = doublex4;
-  static __device__ __forceinline__ int row(int lane, int v) { return 4 * v + lane / 16; }
-};
 
 // Cut colour step for up to kMaxCols columns, one block per patch: residual
 // rows of all columns, dense local solve, and the update (two-buffer form, see
