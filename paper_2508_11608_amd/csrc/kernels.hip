@@ -249,22 +249,33 @@ struct FaceWArgs {
 //   C_T(i) = (E_T x_T)_i + sum_{ghost faces F of T} sum_m gc_m trace_m(i_dir) W_m(F)(i_t),
 // with E_T the cut-cell matrix or the uncut stiffness and W the face pre-pass
 // output, so that the operator kernel adds one value per special cell and
-// node.  CPB cells per 64-thread block, one thread per cell node, the columns
-// together.  A cut cell's E_T is symmetric and read as its packed upper
-// triangle, (k+1)^d ((k+1)^d + 1) / 2 entries instead of (k+1)^{2d}, staged in
-// LDS by the cell's threads (consecutive threads, consecutive entries).
-template <int D, int K>
+// node.  CPB cells per block, one thread per cell node and CT of the NCOL
+// columns, the NCOL / CT column slots in waves of their own.  A cut cell's E_T
+// is symmetric and read as its packed upper triangle, (k+1)^d ((k+1)^d + 1) / 2
+// entries instead of (k+1)^{2d}, staged in LDS by the cell's threads of all
+// slots (consecutive threads, consecutive entries).  The matrices' bytes bound
+// the kernel; a cell's own chain (its record, its matrix, its ghost terms) hides
+// only behind other waves and behind loads in flight, hence 4 waves on a
+// matrix where there are columns for them, and the ghost terms of a direction
+// read at once, a side without a face read as face 0 and dropped.
+// 8 columns, Q3, 16 569 special cells (275 MB of FP64 matrices): FP64 497 -> 231 us,
+// FP32 220 -> 123 us; Q2 disc of 512^2, one column: 6.2 -> 4.7 us.
+template <int D, int K, int NCOL>
 struct CellShape {
   static constexpr int NL = Shape<D, K>::NL;
   static constexpr int CPB = 64 / NL;
-  static_assert(CPB >= 1, "one thread per cell node");
+  static constexpr int NW = NCOL < 4 ? 1 : 4;  // column slots, a wave each
+  static constexpr int CT = NCOL / NW;         // columns of a slot
+  static constexpr int TH = 64 * NW;
+  static_assert(CPB >= 1 && CT * NW == NCOL, "one thread per cell node and slot");
 };
 
 template <int D, int K, typename T, int NCOL>
 __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, const T* __restrict__ W,
                                              T* __restrict__ C, int ncol) {
   using S = Shape<D, K>;
-  constexpr int N1 = S::N1, NL = S::NL, CPB = CellShape<D, K>::CPB, NF = 2 * D;
+  using H = CellShape<D, K, NCOL>;
+  constexpr int N1 = S::N1, NL = S::NL, CPB = H::CPB, CT = H::CT, NF = 2 * D;
   constexpr int NT = Pow<N1, D - 1>::v;
   constexpr int NPK = NL * (NL + 1) / 2;  // entries of a packed symmetric cell matrix
   // column group blockIdx.y of at most NCOL columns
@@ -274,8 +285,10 @@ __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, 
   ncol = ncol - (int)blockIdx.y * NCOL < NCOL ? ncol - (int)blockIdx.y * NCOL : NCOL;
   __shared__ T xs[CPB][NL][NCOL];
   __shared__ T epk[CPB][NPK];
-  const int lc = threadIdx.x / NL;
-  const int i = threadIdx.x % NL;
+  const int slot = H::NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int c0 = slot * CT, nc = ncol - c0;  // the slot's columns (none if nc <= 0)
+  const int lc = threadIdx.x % 64 / NL;
+  const int i = threadIdx.x % 64 % NL;
   const int64_t t = (int64_t)blockIdx.x * CPB + lc;
   const bool on = lc < CPB && t < L.n_spec;
   int il[3] = {0, 0, 0};
@@ -295,65 +308,75 @@ __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, 
     }
     const int64_t node = lat(D, L.nn, I);
 #pragma unroll
-    for (int c = 0; c < NCOL; ++c) xs[lc][i][c] = c < ncol ? x[c * L.n_nodes + node] : (T)0;
+    for (int c = 0; c < CT; ++c) xs[lc][i][c0 + c] = c < nc ? x[(c0 + c) * L.n_nodes + node] : (T)0;
     // a cut cell's matrix, read once as its packed upper triangle (the cell's
     // threads read consecutive entries, G loads in flight per thread) and
     // staged for all rows
     if (info[0] >= 0) {
       const T* P = L.cut_packed_t<T>() + (int64_t)info[0] * NPK;
-      constexpr int NR = (NPK + NL - 1) / NL, G = 8;
+      constexpr int RT = NL * H::NW, NR = (NPK + RT - 1) / RT, G = NR < 16 ? NR : 8;
+      const int e0 = slot * NL + i;
 #pragma unroll
       for (int r0 = 0; r0 < NR; r0 += G) {
         T v[G];
 #pragma unroll
         for (int r = 0; r < G; ++r) {
-          const int e = (r0 + r) * NL + i;
-          v[r] = (r0 + r < NR && e < NPK) ? P[e] : (T)0;
+          const int e = (r0 + r) * RT + e0;
+          v[r] = P[e < NPK ? e : NPK - 1];
         }
 #pragma unroll
         for (int r = 0; r < G; ++r) {
-          const int e = (r0 + r) * NL + i;
-          if (r0 + r < NR && e < NPK) epk[lc][e] = v[r];
+          const int e = (r0 + r) * RT + e0;
+          if (e < NPK) epk[lc][e] = v[r];
+        }
+      }
+    }
+  }
+  // ghost terms before the barrier: their loads do not wait for the staged x
+  T acc[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) acc[c] = 0;
+  if (on && nc > 0 && L.n_faces > 0) {
+    const int64_t wcol = L.n_faces * K * NT;
+    const double* d0 = L.tables + S::T_D0;
+    const double* d1 = L.tables + S::T_D1;
+    const double* gc = L.tables + S::T_GC;
+#pragma unroll
+    for (int dir = 0; dir < D; ++dir) {
+      int it = 0, st = 1;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        if (a == dir) continue;
+        it += il[a] * st;
+        st *= N1;
+      }
+      T w[2][K][CT];
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        const int fid = info[1 + 2 * dir + side];
+        const T* p = W + (int64_t)(fid < 0 ? 0 : fid) * K * NT + it + c0 * wcol;
+#pragma unroll
+        for (int m = 0; m < K; ++m)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) w[side][m][c] = p[(c < nc ? c : 0) * wcol + m * NT];
+      }
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        const bool face = info[1 + 2 * dir + side] >= 0;
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+          const T sg = (T)(gc[m] * (side == 1 ? d1[m * N1 + il[dir]] : -d0[m * N1 + il[dir]]));
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[c] = face ? acc[c] + sg * w[side][m][c] : acc[c];
         }
       }
     }
   }
   __syncthreads();
-  if (!on) return;
-  T acc[NCOL];
+  if (!on || nc <= 0) return;
+  T cell[CT];
 #pragma unroll
-  for (int c = 0; c < NCOL; ++c) acc[c] = 0;
-  // ghost terms first: their loads do not wait for the staged x
-  const int64_t wcol = L.n_faces * K * NT;
-  const double* d0 = L.tables + S::T_D0;
-  const double* d1 = L.tables + S::T_D1;
-  const double* gc = L.tables + S::T_GC;
-#pragma unroll
-  for (int dir = 0; dir < D; ++dir) {
-    int it = 0, st = 1;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (a == dir) continue;
-      it += il[a] * st;
-      st *= N1;
-    }
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      const int fid = info[1 + 2 * dir + side];
-      if (fid < 0) continue;
-      const T* w = W + (int64_t)fid * K * NT + it;
-#pragma unroll
-      for (int m = 0; m < K; ++m) {
-        const T sg = (T)(gc[m] * (side == 1 ? d1[m * N1 + il[dir]] : -d0[m * N1 + il[dir]]));
-#pragma unroll
-        for (int c = 0; c < NCOL; ++c)
-          if (c < ncol) acc[c] += sg * w[c * wcol + m * NT];
-      }
-    }
-  }
-  T cell[NCOL];
-#pragma unroll
-  for (int c = 0; c < NCOL; ++c) cell[c] = 0;
+  for (int c = 0; c < CT; ++c) cell[c] = 0;
   if (info[0] >= 0) {
     // entry (a, b), a <= b, of the packed upper triangle sits at a (2 NL - a + 1) / 2 + b - a;
     // row i of E is (j, i) for j < i and (i, j) from the diagonal on
@@ -363,7 +386,7 @@ __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, 
       const int q = j < i ? j * (2 * NL - j + 1) / 2 + (i - j) : rowi + (j - i);
       const T e = epk[lc][q];
 #pragma unroll
-      for (int c = 0; c < NCOL; ++c) cell[c] += e * xs[lc][j][c];
+      for (int c = 0; c < CT; ++c) cell[c] += e * xs[lc][j][c0 + c];
     }
   } else {
     const T* row = L.kcell_t<T>() + S::T_KCELL + i * NL;
@@ -371,16 +394,16 @@ __device__ __forceinline__ void cell_ax_body(KLevel L, const T* __restrict__ x, 
     for (int j = 0; j < NL; ++j) {
       const T e = row[j];
 #pragma unroll
-      for (int c = 0; c < NCOL; ++c) cell[c] += e * xs[lc][j][c];
+      for (int c = 0; c < CT; ++c) cell[c] += e * xs[lc][j][c0 + c];
     }
   }
 #pragma unroll
-  for (int c = 0; c < NCOL; ++c)
-    if (c < ncol) C[c * L.n_spec * NL + t * NL + i] = cell[c] + acc[c];
+  for (int c = 0; c < CT; ++c)
+    if (c < nc) C[(c0 + c) * L.n_spec * NL + t * NL + i] = cell[c] + acc[c];
 }
 
 template <int D, int K, typename T, int NCOL>
-__global__ __launch_bounds__(64) void k_cell_ax(KLevel L, const T* __restrict__ x, const T* __restrict__ W,
+__global__ __launch_bounds__((CellShape<D, K, NCOL>::TH)) void k_cell_ax(KLevel L, const T* __restrict__ x, const T* __restrict__ W,
                                                 T* __restrict__ C, int ncol) {
   cell_ax_body<D, K, T, NCOL>(L, x, W, C, ncol);
 }
@@ -2692,14 +2715,16 @@ hipError_t launch_apply(int d, int k, const KLevel& L, const T* x, const T* b, T
       }
     }
     if (L.n_spec > 0 || t_rec) {
-      constexpr int CPB = dev::CellShape<D.value, K.value>::CPB;
+      using One = dev::CellShape<D.value, K.value, 1>;
+      using Many = dev::CellShape<D.value, K.value, kMaxCols>;
+      constexpr int CPB = One::CPB;
       const dim3 g(std::max(1u, static_cast<unsigned>((L.n_spec + CPB - 1) / CPB)),
                    ncol == 1 ? 1 : (ncol + kMaxCols - 1) / kMaxCols);
       if (ncol == 1) {
-        if (!record<64>(g, dim3(64), dev::CellAxArgs<D.value, K.value, T, 1>{L, x, W, C, 1}))
-          hipLaunchKernelGGL((dev::k_cell_ax<D.value, K.value, T, 1>), g, dim3(64), 0, s, L, x, W, C, 1);
-      } else if (!record<64>(g, dim3(64), dev::CellAxArgs<D.value, K.value, T, kMaxCols>{L, x, W, C, ncol})) {
-        hipLaunchKernelGGL((dev::k_cell_ax<D.value, K.value, T, kMaxCols>), g, dim3(64), 0, s, L, x, W, C, ncol);
+        if (!record<One::TH>(g, dim3(One::TH), dev::CellAxArgs<D.value, K.value, T, 1>{L, x, W, C, 1}))
+          hipLaunchKernelGGL((dev::k_cell_ax<D.value, K.value, T, 1>), g, dim3(One::TH), 0, s, L, x, W, C, 1);
+      } else if (!record<Many::TH>(g, dim3(Many::TH), dev::CellAxArgs<D.value, K.value, T, kMaxCols>{L, x, W, C, ncol})) {
+        hipLaunchKernelGGL((dev::k_cell_ax<D.value, K.value, T, kMaxCols>), g, dim3(Many::TH), 0, s, L, x, W, C, ncol);
       }
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
