@@ -71,7 +71,7 @@ def parse():
                          "for the comma-separated finest levels L (k = 1..3, n_c = 1..4), beside the paper's numbers")
     ap.add_argument("--rate", type=float, default=0.8, help="arrival rate as a fraction of the saturation rate")
     ap.add_argument("--small-cut-launch", type=int, default=None,
-                    help="cut colour steps with fewer patches run with twice the threads per patch (default 1536)")
+                    help="cut colour steps with fewer patches run with more threads per patch (default 1536)")
     ap.add_argument("--no-graphs", action="store_true",
                     help="launch every V-cycle kernel by kernel instead of replaying captured HIP graphs")
     return ap.parse_args()

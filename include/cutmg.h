@@ -131,7 +131,7 @@ cmg_status cmg_device_bytes(const cmg_problem* p, int flags, size_t* bytes);
 cmg_status cmg_set_precision(cmg_problem* p, int fp32);
 
 /* Launch shapes chosen by launch size: cut colour steps of fewer than
- * small_cut_launch patches run with twice the threads per patch block
+ * small_cut_launch patches run with more threads per patch block
  * (default 1536; 0 never, a large value always), and the grid-stride operator
  * and interior-patch kernels launch at most max_blocks blocks per column
  * (default 2048, >= 1).  The arithmetic of every node is the same in every
@@ -160,7 +160,7 @@ cmg_status cmg_set_ghost_coupling(cmg_problem* p, int mode);
  * as replays of HIP graphs: the kernel sequence of a V-cycle is captured once
  * per precision and column count (on a stream of the problem's own) and each
  * V-cycle is one graph launch on the caller's stream, so the host does not
- * issue ~270 kernel launches per V-cycle.  The graphs hold kernel nodes only
+ * issue its 100 to 300 kernel launches.  The graphs hold kernel nodes only
  * (no memset nodes); while kernels are timed (cmg_timing), every timed launch
  * is a graph of its own, launched between two events recorded on the stream.
  * Results are bit for bit those of kernel-by-kernel launches.  enable = 0 launches kernel by
@@ -250,14 +250,12 @@ cmg_status cmg_vcycle_solve(cmg_problem* p, const double* b, double* x, double r
 /* Several right-hand sides at once (1 <= nrhs <= 8).  Column c of r, z, b and x
  * starts at c * n_L (n_L = cmg_ndofs of the finest level), canonical order.
  *
- * cmg_vcycle_multi: z_c = B r_c for every column.  In FP64 the columns run
- * through the same kernels as cmg_vcycle (one grid row per column) and the
- * results equal nrhs single V-cycles bit for bit.  In FP32 (cmg_set_precision)
- * the cut-patch local solves read each inverse once for all columns and apply
- * it on the matrix cores (16x16x4 FP32 MFMA, FP32 accumulation), also for
- * nrhs = 1, so the result differs from cmg_vcycle by rounding only.  In both
- * precisions a column's result is independent of the other columns and of
- * nrhs, bit for bit.
+ * cmg_vcycle_multi: z_c = B r_c for every column.  The cut colour steps read
+ * each cell matrix and inverse once for all columns and apply them on the
+ * matrix cores (16x16x4 MFMA of the V-cycle's precision, accumulation in the
+ * same), also for nrhs = 1, so the result differs from cmg_vcycle by rounding
+ * only.  In both precisions a column's result is independent of the other
+ * columns and of nrhs, bit for bit.
  *
  * cmg_solve_multi: nrhs independent PCG recurrences (own alpha, beta and
  * stopping test per column) that share one multi-column V-cycle and one
@@ -274,8 +272,8 @@ cmg_status cmg_solve_multi(cmg_problem* p, int nrhs, const double* b, double* x,
 
 /* Grouped V-cycles of several problems (the V-cycle of Section 2.2 for each).
  * For callers that solve many small problems at once, such as a solve server
- * (the V-cycle of a small problem is bound by its ~270 kernel launches, not by
- * memory traffic).  A group holds 1..8 distinct uploaded problems with the same
+ * (the V-cycle of a small problem is bound by its 100 or more dependent kernel
+ * launches, not by memory traffic).  A group holds 1..8 distinct uploaded problems with the same
  * dimension, degree, level count, coarse mesh, box, V-cycle precision and
  * device, all with the exact ghost coupling: their levels share one lattice.
  * cmg_group_create records every member's V-cycle in the form that

@@ -744,7 +744,7 @@ enum KernelKind {
 // ---- device-side building blocks on the internal lattice vectors ------------
 // multi = false: the single-column work vectors (ncol = 1); multi = true: the
 // first ncol columns of the multi-column work vectors (kMaxCols columns,
-// n_nodes apart), and in FP32 the matrix-core cut-patch solves, whatever ncol
+// n_nodes apart) and the matrix-core cut colour steps, whatever ncol
 // is, so that a column's result does not depend on how many columns run with it.
 
 template <typename T>
@@ -1157,7 +1157,7 @@ void drop_graphs(cmg_problem* P) {
 // V-cycle is fixed for a problem, a precision and a column count, so it is
 // captured once (on the problem's own capture stream: the caller's stream may
 // be the null stream, which cannot be captured) and replayed: one host call
-// instead of ~270 kernel launches, whose host cost otherwise exceeds the GPU
+// instead of 100 to 300 kernel launches, whose host cost otherwise exceeds the GPU
 // time of the short coarse-level kernels.  The graph holds kernel nodes only
 // (every buffer is cleared by kernels; no memset nodes).  While kernels are
 // timed, the timed launches are pieces of their own, bracketed by events
