@@ -279,11 +279,13 @@ cmg_status cmg_solve_multi(cmg_problem* p, int nrhs, const double* b, double* x,
  * cmg_group_create records every member's V-cycle in the form that
  * cmg_vcycle_multi runs with nrhs = 1 (allocating its multi-column vectors as
  * that call does) and checks that the members' kernel sequences match step by
- * step, which holds when every member has cut patches in the same colours on
- * every level; otherwise it returns CMG_EINVAL and keeps nothing.  It uploads
- * the members' kernel arguments as one device table.  Each step of the
- * group's V-cycle is then one launch over all members (blockIdx.z selects the
- * member), and the grouped V-cycle is replayed from one HIP graph.  The group
+ * step on every level, which holds when every member has cut patches in the
+ * same colours on every level; otherwise it returns CMG_EINVAL and keeps
+ * nothing.  It uploads the members' kernel arguments as one device table.  Each
+ * step of the group's V-cycle is then one launch over all members that have it
+ * (blockIdx.z selects the member; a member applies its smallest levels as one
+ * dense matrix where the level has at most 2048 DoFs, and has no steps on the
+ * levels below), and the grouped V-cycle is replayed from one HIP graph.  The group
  * keeps the precision and ghost coupling its members had when it was created.
  * A member stays usable alone, but no other call may run on a member while a
  * call of its group runs, and a group must be destroyed before any of its

@@ -879,18 +879,22 @@ cmg_status restrict_(cmg_problem* P, int l, const T* rf, hipStream_t s, int ncol
 
 // V-cycle of the levels bottom..top on the lattice vectors of precision T:
 // x_top = B b_top, zero initial guess; level `bottom` is solved by its dense
-// matrix (coarse).
+// matrix (coarse).  The segments of grouped launches: down each level, the
+// dense product, up each level, in an order that holds for every bottom.
 template <typename T>
 cmg_status vcycle_levels(cmg_problem* P, int bottom, int top, hipStream_t s, int ncol, bool multi) {
   for (int l = top; l > bottom; --l) {
+    cmg::set_launch_segment(2 * (top - l));
     Vecs<T>& v = work<T>(P->lv[l], multi);
     TRY(zero_active<T>(P, l, v.x, s, ncol));
     TRY(smooth<T>(P, l, false, s, ncol, multi));
     TRY(apply_lat<T>(P, l, v.x, v.b, v.r, s, ncol, multi));
     TRY(restrict_<T>(P, l, v.r, s, ncol, multi));
   }
+  cmg::set_launch_segment(2 * (top - bottom) + 1);
   TRY(coarse<T>(P, s, ncol, multi, bottom));
   for (int l = bottom + 1; l <= top; ++l) {
+    cmg::set_launch_segment(2 * (top + 1) + l);
     TRY(prolong_add<T>(P, l, s, ncol, multi));
     TRY(smooth<T>(P, l, true, s, ncol, multi));
   }
@@ -1332,9 +1336,9 @@ struct cmg_group {
   bool fp32 = false;
   struct Step {
     const void* fn;  // grouped kernel
-    dim3 grid;       // largest member grid, z = members
+    dim3 grid;       // largest member grid, z = the members that take part
     dim3 block;
-    size_t off;      // the members' argument records in tab
+    size_t off;      // their argument records in tab
   };
   std::vector<Step> steps;
   unsigned char* tab = nullptr;  // device: argument records, one array per step
@@ -1363,7 +1367,10 @@ void group_release(cmg_group* g) {
 
 // Records every member's lattice V-cycle (the multi-column form with one
 // column), checks that the members' launch sequences match step by step and
-// uploads the argument records.
+// uploads the argument records.  A segment of the V-cycle (see vcycle_levels)
+// is launched over the members that have it: a member whose smallest levels are
+// one dense matrix takes no part in the steps of those levels.  Every member
+// keeps its own sequence of kernels, and so its own bits.
 template <typename T>
 cmg_status group_plan(cmg_group* g) {
   const size_t G = g->m.size();
@@ -1374,34 +1381,45 @@ cmg_status group_plan(cmg_group* g) {
     cmg::set_launch_recorder(nullptr);
     TRY(st);
   }
-  const size_t ns = rec[0].size();
-  size_t bytes = 0;
-  for (size_t i = 1; i < G; ++i)
-    if (rec[i].size() != ns)
-      return fail(CMG_EINVAL, "group members differ in their V-cycle steps (member " + std::to_string(i) + ")");
-  for (size_t j = 0; j < ns; ++j) {
-    const cmg::LaunchRecord& r0 = rec[0][j];
-    cmg_group::Step st{r0.fn, dim3(0, 0, static_cast<unsigned>(G)), dim3(r0.block), bytes};
+  std::vector<size_t> at(G, 0);  // the members' next records
+  std::vector<unsigned char> host;
+  for (;;) {
+    // the next segment, and the members that have it with their number of steps
+    int seg = -1;
+    for (size_t i = 0; i < G; ++i)
+      if (at[i] < rec[i].size() && (seg < 0 || rec[i][at[i]].segment < seg)) seg = rec[i][at[i]].segment;
+    if (seg < 0) break;
+    std::vector<size_t> who;
+    size_t ns = 0;
     for (size_t i = 0; i < G; ++i) {
-      const cmg::LaunchRecord& r = rec[i][j];
-      if (!r.fn || r.fn != r0.fn || r.block != r0.block || r.args.size() != r0.args.size())
-        return fail(CMG_EINVAL, "group members differ in V-cycle step " + std::to_string(j) + " (member " +
-                                    std::to_string(i) + ")");
-      st.grid.x = std::max(st.grid.x, r.grid[0]);
-      st.grid.y = std::max(st.grid.y, r.grid[1]);
+      size_t n = 0;
+      while (at[i] + n < rec[i].size() && rec[i][at[i] + n].segment == seg) ++n;
+      if (n == 0) continue;
+      if (who.empty()) ns = n;
+      if (n != ns)
+        return fail(CMG_EINVAL, "group members differ in their V-cycle steps (member " + std::to_string(i) + ")");
+      who.push_back(i);
     }
-    g->steps.push_back(st);
-    bytes += (G * r0.args.size() + 255) / 256 * 256;
+    for (size_t j = 0; j < ns; ++j) {
+      const cmg::LaunchRecord& r0 = rec[who[0]][at[who[0]] + j];
+      cmg_group::Step st{r0.fn, dim3(0, 0, static_cast<unsigned>(who.size())), dim3(r0.block), host.size()};
+      for (size_t i : who) {
+        const cmg::LaunchRecord& r = rec[i][at[i] + j];
+        if (!r.fn || r.fn != r0.fn || r.block != r0.block || r.args.size() != r0.args.size())
+          return fail(CMG_EINVAL, "group members differ in V-cycle step " + std::to_string(g->steps.size()) +
+                                      " (member " + std::to_string(i) + ")");
+        st.grid.x = std::max(st.grid.x, r.grid[0]);
+        st.grid.y = std::max(st.grid.y, r.grid[1]);
+        host.insert(host.end(), r.args.begin(), r.args.end());
+      }
+      g->steps.push_back(st);
+      host.resize((host.size() + 255) / 256 * 256);
+    }
+    for (size_t i : who) at[i] += ns;
   }
-  std::vector<unsigned char> host(bytes);
-  for (size_t j = 0; j < ns; ++j)
-    for (size_t i = 0; i < G; ++i) {
-      const std::vector<unsigned char>& a = rec[i][j].args;
-      std::memcpy(host.data() + g->steps[j].off + i * a.size(), a.data(), a.size());
-    }
   std::lock_guard<std::recursive_mutex> lock(cmg::device_mutex());
-  HIP_TRY(hipMalloc(&g->tab, bytes));
-  HIP_TRY(hipMemcpy(g->tab, host.data(), bytes, hipMemcpyHostToDevice));
+  HIP_TRY(hipMalloc(&g->tab, host.size()));
+  HIP_TRY(hipMemcpy(g->tab, host.data(), host.size(), hipMemcpyHostToDevice));
   return settle();
 }
 

@@ -118,14 +118,18 @@ int tables_size(int d, int k);
 // Launches without a grouped form append an empty record (fn == nullptr).
 // While recording, the operator pre-passes, interior colour steps and zero
 // fills are recorded also where they have no work, so that problems of one
-// lattice shape record the same sequence of kernels.
+// lattice shape record the same sequence of kernels on every level that they
+// run.  Which levels they run differs (the smallest ones may be one dense
+// matrix), so every record carries the segment of the V-cycle it belongs to.
 struct LaunchRecord {
   const void* fn = nullptr;
+  int segment = 0;
   unsigned grid[2] = {0, 0};
   unsigned block = 0;
   std::vector<unsigned char> args;
 };
 void set_launch_recorder(std::vector<LaunchRecord>* rec);  // nullptr: launch again
+void set_launch_segment(int segment);                      // of the records that follow
 bool launch_recording();
 
 // Every multigrid launcher works on ncol columns at once (blockIdx.y = column):

@@ -2646,6 +2646,7 @@ inline unsigned blocks(int64_t n, int b = 256) { return static_cast<unsigned>((n
 
 // Launch recorder of the calling thread (see set_launch_recorder).
 thread_local std::vector<LaunchRecord>* t_rec = nullptr;
+thread_local int t_segment = 0;
 
 // While recording: append the grouped form of a launch and return true.
 template <int LB, typename A>
@@ -2653,6 +2654,7 @@ bool record(dim3 g, dim3 b, const A& a) {
   if (!t_rec) return false;
   LaunchRecord r;
   r.fn = reinterpret_cast<const void*>(&dev::k_grouped<LB, A>);
+  r.segment = t_segment;
   r.grid[0] = g.x;
   r.grid[1] = g.y;
   r.block = b.x;
@@ -2666,6 +2668,7 @@ bool record(dim3 g, dim3 b, const A& a) {
 bool record_none() {
   if (!t_rec) return false;
   t_rec->push_back(LaunchRecord{});
+  t_rec->back().segment = t_segment;
   return true;
 }
 
@@ -2687,7 +2690,11 @@ hipError_t dispatch(int d, int k, F&& f) {
 
 }  // namespace
 
-void set_launch_recorder(std::vector<LaunchRecord>* rec) { t_rec = rec; }
+void set_launch_recorder(std::vector<LaunchRecord>* rec) {
+  t_rec = rec;
+  t_segment = 0;
+}
+void set_launch_segment(int segment) { t_segment = segment; }
 bool launch_recording() { return t_rec != nullptr; }
 
 int tables_size(int d, int k) {
