@@ -113,7 +113,8 @@ cmg_status cmg_setup_host(const cmg_levelset* ls, const cmg_params* prm, cmg_pro
  * (no-op for a device problem).  Synchronous. */
 cmg_status cmg_upload(cmg_problem* p);
 
-/* Device memory in bytes that the problem occupies once uploaded.  flags bit 0:
+/* Device memory in bytes that the problem occupies once uploaded and once its
+ * first V-cycle has run (see cmg_vcycle).  flags bit 0:
  * include the FP32 copies of the mixed-precision V-cycle; bit 1: include the
  * buffers of the multi-column calls (8 columns of work vectors on every level,
  * the multi-column Krylov vectors and, with bit 0, the tiled FP32 inverses);
@@ -218,7 +219,12 @@ cmg_status cmg_coarse_solve(cmg_problem* p, const double* b, double* x, void* st
  * Section 2.2, the standard V-cycle with one pre- and one post-smoothing step
  * of the smoother of eq. (smoother-split); Section 4 for the one-step setting).
  * The post-smoother runs the pre-smoother's colour steps in reverse, so B is
- * symmetric and usable in CG. */
+ * symmetric and usable in CG.
+ * With the exact ghost coupling, the V-cycle of the levels up to the finest one
+ * below the top that has at most 2048 DoFs is applied as one dense matrix
+ * (equal to rounding).  The first V-cycle of a problem and precision, in
+ * whichever call, makes that matrix: it allocates and waits for the GPU, on a
+ * stream of the problem's own. */
 cmg_status cmg_vcycle(cmg_problem* p, const double* r, double* z, void* stream);
 
 /* Solve A_L x = b (paper Section 2.1, eq. (weak-equation) in matrix form) by

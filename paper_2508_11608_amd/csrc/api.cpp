@@ -132,7 +132,7 @@ struct cmg_problem {
   double* coarse64 = nullptr;
   float* coarse32 = nullptr;
   int dense_level = 0;        // the V-cycle of levels 0..dense_level as one dense matrix (0: none), see dense_level_of
-  double* dense64 = nullptr;
+  double* dense64 = nullptr;  // made by the first V-cycle (ensure_dense)
   float* dense32 = nullptr;
   bool fp32_ready = false;
   bool fp32 = false;  // precision of the V-cycle
@@ -240,16 +240,15 @@ float* dense_op<float>(cmg_problem* P) { return P->dense32; }
 // bytes (33 MB at the limit, about 10 us) in place of the chain of its levels:
 // V-cycle 382 -> 159 us (disc, Q2, 32^2: levels 1 and 2), 1341 -> 939 us (circle,
 // Q2, 512^2: 1 to 3), 1228 -> 902 us (ball, Q2, 32^3: 1).  Making it costs the
-// set-up n columns of the V-cycle it replaces, 1 ms (n = 529) to 9 ms (n = 1,701,
-// 5% of that set-up), which one to three solves give back; at n = 4,096 it would
-// be tens of ms.  0: none (level 0 has its exact inverse anyway).
+// first V-cycle n columns of the one it replaces, 1 ms (n = 529) to 9 ms (n =
+// 1,701), which one to three solves give back; at n = 4,096 it would be tens of
+// ms.  0: none (level 0 has its exact inverse anyway).
 constexpr int64_t kDenseMax = 2048;
 int dense_level_of(const cmg::Hierarchy& H) {
   for (int l = static_cast<int>(H.levels.size()) - 2; l >= 1; --l)
     if (H.levels[l].n_dofs <= kDenseMax) return l;
   return 0;
 }
-cmg_status build_dense(cmg_problem* P);
 
 template <typename T>
 cmg_status upload(std::vector<void*>& owned, const T* host, size_t n, T** dptr) {
@@ -516,7 +515,7 @@ cmg_status upload_all(cmg_problem* P) {
   P->nblk = static_cast<int>(std::min<int64_t>(1024, (n + 255) / 256));
   TRY(alloc_zero(own, static_cast<size_t>(P->nblk), &P->part));
   HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&P->part_host), P->nblk * sizeof(double), hipHostMallocDefault));
-  TRY(build_dense(P));
+  P->dense_level = dense_level_of(P->H);
   return settle();
 }
 
@@ -553,11 +552,6 @@ cmg_status ensure_fp32(cmg_problem* P) {
     if (d.n_region > 0) TRY(alloc_zero(own, h.n_nodes, &d.v32.x1));
   }
   TRY(upload_f32(own, P->H.coarse_inv, &P->coarse32));
-  if (P->dense_level > 0) {
-    const int64_t n = P->H.levels[P->dense_level].n_dofs;
-    TRY(alloc_zero(own, static_cast<size_t>(n * n), &P->dense32));
-    HIP_TRY(cmg::launch_round(n * n, P->dense64, P->dense32, nullptr));
-  }
   TRY(settle());
   P->fp32_ready = true;
   return CMG_OK;
@@ -908,48 +902,101 @@ cmg_status vcycle_lattice(cmg_problem* P, hipStream_t s, int ncol = 1, bool mult
   return vcycle_levels<T>(P, P->ghost_local ? 0 : P->dense_level, P->H.cfg.n_levels - 1, s, ncol, multi);
 }
 
-// The dense V-cycle of the levels 0..dense_level: the FP64 V-cycle of those
-// levels applied to the unit vectors, a batch of columns per launch sequence, on
-// work vectors that are released again.  Part of the set-up (null stream).
-cmg_status build_dense(cmg_problem* P) {
-  const int l0 = dense_level_of(P->H);
-  if (l0 == 0) return CMG_OK;
+// For the life of one: this thread may allocate while the caller captures a
+// stream (a V-cycle launched kernel by kernel can be captured).
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// The matrix M = dense64 of the V-cycle of the levels 0..dense_level: their FP64
+// V-cycle applied to the unit vectors on stream s, a batch of columns per launch
+// sequence, on work vectors that are released again (one allocation).
+cmg_status build_dense(cmg_problem* P, double* M, hipStream_t s) {
+  const int l0 = P->dense_level;
   const int64_t n = P->H.levels[l0].n_dofs;
-  TRY(alloc_zero(P->owned, static_cast<size_t>(n * n), &P->dense64));
-  // about 128 MB of work vectors at a time
-  size_t per = 0;
+  auto up = [](size_t e) { return (e + 31) / 32 * 32; };  // 256-byte pieces
+  size_t per = 0;                                          // entries of one column
   for (int l = 0; l <= l0; ++l) {
     const DevLevel& d = P->lv[l];
-    per += 8 * (4 * static_cast<size_t>(d.kl64.n_nodes) + d.n_w + d.n_c + static_cast<size_t>(d.max_cut_nodes));
+    per += 4 * static_cast<size_t>(d.kl64.n_nodes) + d.n_w + d.n_c + static_cast<size_t>(d.max_cut_nodes);
   }
-  const int64_t batch = std::min<int64_t>(n, std::max<int64_t>(cmg::kMaxCols, (int64_t{128} << 20) / static_cast<int64_t>(per)));
+  // about 128 MB of work vectors at a time
+  const int64_t batch = std::min<int64_t>(n, std::max<int64_t>(cmg::kMaxCols, (int64_t{16} << 20) / static_cast<int64_t>(per)));
   const size_t C = static_cast<size_t>(batch);
-  std::vector<void*> tmp;
-  auto run = [&]() -> cmg_status {
+  size_t total = 0;
+  std::vector<Vecs<double>> own(l0 + 1);
+  for (int l = 0; l <= l0; ++l) own[l] = P->lv[l].m64;
+  auto place = [&](double* base) {
+    total = 0;
     for (int l = 0; l <= l0; ++l) {
       DevLevel& d = P->lv[l];
+      Vecs<double>& v = d.m64;
+      auto take = [&](double** q, size_t e) {
+        *q = base && e > 0 ? base + total : nullptr;
+        total += up(C * e);
+      };
       const size_t nn = static_cast<size_t>(d.kl64.n_nodes);
-      for (double** v : {&d.m64.x, &d.m64.b, &d.m64.r, &d.m64.x1}) TRY(alloc_zero(tmp, C * nn, v));
-      TRY(alloc_zero(tmp, C * d.n_w, &d.m64.W));
-      TRY(alloc_zero(tmp, C * d.n_c, &d.m64.C));
-      TRY(alloc_zero(tmp, C * static_cast<size_t>(d.max_cut_nodes), &d.m64.dbuf));
-      if (d.n_region == 0) d.m64.x1 = nullptr;
+      take(&v.x, nn);
+      take(&v.b, nn);
+      take(&v.r, nn);
+      take(&v.x1, d.n_region > 0 ? nn : 0);
+      take(&v.W, d.n_w);
+      take(&v.C, d.n_c);
+      take(&v.dbuf, static_cast<size_t>(d.max_cut_nodes));
     }
+  };
+  place(nullptr);
+  void* tmp = nullptr;
+  const unsigned timed = P->timing_mask;
+  auto run = [&]() -> cmg_status {
+    if (hipMalloc(&tmp, total * sizeof(double)) != hipSuccess) return fail(CMG_ENOMEM, "device allocation failed");
+    place(static_cast<double*>(tmp));
+    HIP_TRY(hipMemsetAsync(tmp, 0, total * sizeof(double), s));
     DevLevel& D = P->lv[l0];
     for (int64_t c0 = 0; c0 < n; c0 += batch) {
       const int nc = static_cast<int>(std::min(batch, n - c0));
-      HIP_TRY(cmg::launch_units(D.kl64.dof_node, n, c0, nc, D.m64.b, D.kl64.n_nodes, nullptr));
-      TRY(vcycle_levels<double>(P, 0, l0, nullptr, nc, true));
-      HIP_TRY(cmg::launch_put_columns(D.kl64.dof_node, n, c0, nc, D.m64.x, D.kl64.n_nodes, P->dense64, nullptr));
+      HIP_TRY(cmg::launch_units(D.kl64.dof_node, n, c0, nc, D.m64.b, D.kl64.n_nodes, s));
+      TRY(vcycle_levels<double>(P, 0, l0, s, nc, true));
+      HIP_TRY(cmg::launch_put_columns(D.kl64.dof_node, n, c0, nc, D.m64.x, D.kl64.n_nodes, M, s));
     }
-    return settle();
+    HIP_TRY(hipStreamSynchronize(s));
+    return CMG_OK;
   };
+  P->timing_mask = 0;  // these launches belong to no V-cycle
   const cmg_status st = run();
-  if (st != CMG_OK) (void)hipStreamSynchronize(nullptr);
-  for (int l = 0; l <= l0; ++l) P->lv[l].m64 = Vecs<double>();
-  for (void* v : tmp) (void)hipFree(v);
-  if (st == CMG_OK) P->dense_level = l0;
+  P->timing_mask = timed;
+  if (st != CMG_OK) (void)hipStreamSynchronize(s);
+  for (int l = 0; l <= l0; ++l) P->lv[l].m64 = own[l];
+  if (tmp) (void)hipFree(tmp);
   return st;
+}
+
+// The dense matrix of the smallest levels in precision T, made by the first
+// V-cycle that runs with it (callers of products, transfers or smoothing steps
+// alone do not pay for it).  Synchronous, on the problem's own stream.
+template <typename T>
+cmg_status ensure_dense(cmg_problem* P) {
+  if (P->ghost_local || P->dense_level == 0 || dense_op<T>(P)) return CMG_OK;
+  std::lock_guard<std::recursive_mutex> lock(cmg::device_mutex());
+  if (std::is_same<T, float>::value) TRY(ensure_dense<double>(P));
+  RelaxedCapture relaxed;
+  if (!P->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking));
+  const int64_t n = P->H.levels[P->dense_level].n_dofs;
+  void* m = nullptr;
+  if (hipMalloc(&m, static_cast<size_t>(n * n) * sizeof(T)) != hipSuccess)
+    return fail(CMG_ENOMEM, "device allocation failed");
+  P->owned.push_back(m);
+  if constexpr (std::is_same<T, float>::value) {
+    HIP_TRY(cmg::launch_round(n * n, P->dense64, static_cast<float*>(m), P->cap_stream));
+    HIP_TRY(hipStreamSynchronize(P->cap_stream));
+    P->dense32 = static_cast<float*>(m);
+  } else {
+    TRY(build_dense(P, static_cast<double*>(m), P->cap_stream));
+    P->dense64 = static_cast<double*>(m);
+  }
+  return CMG_OK;
 }
 
 template <typename T>
@@ -1232,7 +1279,13 @@ cmg_status op_vcycle(cmg_problem* p, const double* r, double* z, hipStream_t s) 
   return gather<T>(p, L, v.x, z, s);
 }
 
+// The dense matrix of the current precision, needed by every V-cycle.
+cmg_status ensure_dense_current(cmg_problem* p) {
+  return p->fp32 ? ensure_dense<float>(p) : ensure_dense<double>(p);
+}
+
 cmg_status vcycle_current(cmg_problem* p, const double* r, double* z, hipStream_t s) {
+  TRY(ensure_dense_current(p));
   return p->fp32 ? op_vcycle<float>(p, r, z, s) : op_vcycle<double>(p, r, z, s);
 }
 
@@ -1265,7 +1318,7 @@ cmg_status prepare_multi(cmg_problem* p) {
     TRY(ensure_multi<float>(p));
     TRY(ensure_tiles(p));
   }
-  return CMG_OK;
+  return ensure_dense_current(p);
 }
 
 
