@@ -224,7 +224,9 @@ cmg_status cmg_coarse_solve(cmg_problem* p, const double* b, double* x, void* st
  * below the top that has at most 2048 DoFs is applied as one dense matrix
  * (equal to rounding).  The first V-cycle of a problem and precision, in
  * whichever call, makes that matrix: it allocates and waits for the GPU, on a
- * stream of the problem's own. */
+ * stream of the problem's own.  It takes at most 128 MiB of scratch while it
+ * does so (a level whose lattices need more is passed over), and none where that
+ * cannot be had; without room for the matrix itself, every level is run. */
 cmg_status cmg_vcycle(cmg_problem* p, const double* r, double* z, void* stream);
 
 /* Solve A_L x = b (paper Section 2.1, eq. (weak-equation) in matrix form) by
@@ -407,7 +409,8 @@ void cmg_destroy(cmg_problem* p);
  * hierarchies are evicted when a new one needs room); a new hierarchy is
  * admitted when its exact footprint (cmg_footprint with the multi-column
  * buffers, plus the batch's b and x columns), computed before its set-up,
- * fits into hbm_budget_bytes; one that exceeds the whole budget finishes with
+ * fits into hbm_budget_bytes (the scratch of its first V-cycle takes only what
+ * the budget has left); one that exceeds the whole budget finishes with
  * status CMG_ENOMEM without being set up.  Batches of different slots
  * overlap on the device.  A batch of one request is joined by the only queued
  * requests of other resident, idle geometries of the same lattice shape

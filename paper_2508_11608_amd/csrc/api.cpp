@@ -132,8 +132,9 @@ struct cmg_problem {
   double* coarse64 = nullptr;
   float* coarse32 = nullptr;
   int dense_level = 0;        // the V-cycle of levels 0..dense_level as one dense matrix (0: none), see dense_level_of
-  double* dense64 = nullptr;  // made by the first V-cycle (ensure_dense)
+  double* dense64 = nullptr;  // made by the first V-cycle (ensure_dense); null: no matrix, every level is run
   float* dense32 = nullptr;
+  bool dense64_tried = false, dense32_tried = false;
   bool fp32_ready = false;
   bool fp32 = false;  // precision of the V-cycle
   bool m64_ready = false, m32_ready = false, tiles_ready = false;
@@ -242,11 +243,18 @@ float* dense_op<float>(cmg_problem* P) { return P->dense32; }
 // Q2, 512^2: 1 to 3), 1228 -> 902 us (ball, Q2, 32^3: 1).  Making it costs the
 // first V-cycle n columns of the one it replaces, 1 ms (n = 529) to 9 ms (n =
 // 1,701), which one to three solves give back; at n = 4,096 it would be tens of
-// ms.  0: none (level 0 has its exact inverse anyway).
+// ms.  It takes work vectors of a batch of columns on the whole lattices, at most
+// kDenseScratch bytes for as long as that lasts; a level whose lattices do not
+// leave room for kMaxCols columns (few DoFs in a large box) is passed over.  0:
+// none (level 0 has its exact inverse anyway).
 constexpr int64_t kDenseMax = 2048;
+constexpr size_t kDenseScratch = size_t{128} << 20;
 int dense_level_of(const cmg::Hierarchy& H) {
-  for (int l = static_cast<int>(H.levels.size()) - 2; l >= 1; --l)
-    if (H.levels[l].n_dofs <= kDenseMax) return l;
+  for (int l = static_cast<int>(H.levels.size()) - 2; l >= 1; --l) {
+    size_t nodes = 0;
+    for (int j = 0; j <= l; ++j) nodes += static_cast<size_t>(H.levels[j].n_nodes);
+    if (H.levels[l].n_dofs <= kDenseMax && nodes <= kDenseScratch / (4 * sizeof(double) * cmg::kMaxCols)) return l;
+  }
   return 0;
 }
 
@@ -899,7 +907,8 @@ cmg_status vcycle_levels(cmg_problem* P, int bottom, int top, hipStream_t s, int
 // exact ghost coupling; with the patch-local one every level is run.
 template <typename T>
 cmg_status vcycle_lattice(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false) {
-  return vcycle_levels<T>(P, P->ghost_local ? 0 : P->dense_level, P->H.cfg.n_levels - 1, s, ncol, multi);
+  const int bottom = P->ghost_local || !dense_op<T>(P) ? 0 : P->dense_level;
+  return vcycle_levels<T>(P, bottom, P->H.cfg.n_levels - 1, s, ncol, multi);
 }
 
 // For the life of one: this thread may allocate while the caller captures a
@@ -910,50 +919,69 @@ struct RelaxedCapture {
   ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
+// Bytes of the work vectors of C columns on the levels 0..dense_level, one
+// allocation; with a base address, they become the levels' multi-column vectors.
+size_t dense_vectors(std::vector<DevLevel>& lv, int l0, size_t C, double* base) {
+  size_t at = 0;
+  for (int l = 0; l <= l0; ++l) {
+    DevLevel& d = lv[l];
+    auto take = [&](double** q, size_t e) {
+      if (base) *q = e > 0 ? base + at : nullptr;
+      at += (C * e + 31) / 32 * 32;  // 256-byte pieces
+    };
+    const size_t nn = static_cast<size_t>(d.kl64.n_nodes);
+    take(&d.m64.x, nn);
+    take(&d.m64.b, nn);
+    take(&d.m64.r, nn);
+    take(&d.m64.x1, d.n_region > 0 ? nn : 0);
+    take(&d.m64.W, d.n_w);
+    take(&d.m64.C, d.n_c);
+    take(&d.m64.dbuf, static_cast<size_t>(d.max_cut_nodes));
+  }
+  return at * sizeof(double);
+}
+
+// The columns of one batch whose work vectors fit into `scratch` bytes (0: not
+// even one's).
+int64_t dense_batch(cmg_problem* P, size_t scratch) {
+  const int64_t n = P->H.levels[P->dense_level].n_dofs;
+  const size_t one = dense_vectors(P->lv, P->dense_level, 1, nullptr);
+  int64_t C = std::min<int64_t>(n, static_cast<int64_t>(scratch / one) + 1);
+  while (C > 0 && dense_vectors(P->lv, P->dense_level, static_cast<size_t>(C), nullptr) > scratch) --C;
+  return C;
+}
+
 // The matrix M = dense64 of the V-cycle of the levels 0..dense_level: their FP64
 // V-cycle applied to the unit vectors on stream s, a batch of columns per launch
-// sequence, on work vectors that are released again (one allocation).
-cmg_status build_dense(cmg_problem* P, double* M, hipStream_t s) {
+// sequence (a column does not depend on the others), on work vectors that are
+// released again.  Without room for those, a column at a time on the problem's
+// own vectors, which no other call may be using then: *made stays false where
+// that cannot be waited for (the caller's stream is being captured).
+cmg_status build_dense(cmg_problem* P, double* M, size_t scratch, hipStream_t user, hipStream_t s, bool* made) {
   const int l0 = P->dense_level;
   const int64_t n = P->H.levels[l0].n_dofs;
-  auto up = [](size_t e) { return (e + 31) / 32 * 32; };  // 256-byte pieces
-  size_t per = 0;                                          // entries of one column
-  for (int l = 0; l <= l0; ++l) {
-    const DevLevel& d = P->lv[l];
-    per += 4 * static_cast<size_t>(d.kl64.n_nodes) + d.n_w + d.n_c + static_cast<size_t>(d.max_cut_nodes);
-  }
-  // about 128 MB of work vectors at a time
-  const int64_t batch = std::min<int64_t>(n, std::max<int64_t>(cmg::kMaxCols, (int64_t{16} << 20) / static_cast<int64_t>(per)));
-  const size_t C = static_cast<size_t>(batch);
-  size_t total = 0;
-  std::vector<Vecs<double>> own(l0 + 1);
-  for (int l = 0; l <= l0; ++l) own[l] = P->lv[l].m64;
-  auto place = [&](double* base) {
-    total = 0;
-    for (int l = 0; l <= l0; ++l) {
-      DevLevel& d = P->lv[l];
-      Vecs<double>& v = d.m64;
-      auto take = [&](double** q, size_t e) {
-        *q = base && e > 0 ? base + total : nullptr;
-        total += up(C * e);
-      };
-      const size_t nn = static_cast<size_t>(d.kl64.n_nodes);
-      take(&v.x, nn);
-      take(&v.b, nn);
-      take(&v.r, nn);
-      take(&v.x1, d.n_region > 0 ? nn : 0);
-      take(&v.W, d.n_w);
-      take(&v.C, d.n_c);
-      take(&v.dbuf, static_cast<size_t>(d.max_cut_nodes));
-    }
-  };
-  place(nullptr);
+  int64_t batch = dense_batch(P, scratch);
   void* tmp = nullptr;
+  const size_t bytes = batch > 0 ? dense_vectors(P->lv, l0, static_cast<size_t>(batch), nullptr) : 0;
+  if (batch > 0 && hipMalloc(&tmp, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    tmp = nullptr;
+  }
+  if (!tmp) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (user && hipStreamIsCapturing(user, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return CMG_OK;
+    HIP_TRY(hipDeviceSynchronize());
+    batch = 1;
+  }
+  std::vector<Vecs<double>> own(l0 + 1);
+  for (int l = 0; l <= l0; ++l) {
+    own[l] = P->lv[l].m64;
+    if (!tmp) P->lv[l].m64 = P->lv[l].v64;
+  }
+  if (tmp) (void)dense_vectors(P->lv, l0, static_cast<size_t>(batch), static_cast<double*>(tmp));
   const unsigned timed = P->timing_mask;
   auto run = [&]() -> cmg_status {
-    if (hipMalloc(&tmp, total * sizeof(double)) != hipSuccess) return fail(CMG_ENOMEM, "device allocation failed");
-    place(static_cast<double*>(tmp));
-    HIP_TRY(hipMemsetAsync(tmp, 0, total * sizeof(double), s));
+    if (tmp) HIP_TRY(hipMemsetAsync(tmp, 0, bytes, s));
     DevLevel& D = P->lv[l0];
     for (int64_t c0 = 0; c0 < n; c0 += batch) {
       const int nc = static_cast<int>(std::min(batch, n - c0));
@@ -970,33 +998,49 @@ cmg_status build_dense(cmg_problem* P, double* M, hipStream_t s) {
   if (st != CMG_OK) (void)hipStreamSynchronize(s);
   for (int l = 0; l <= l0; ++l) P->lv[l].m64 = own[l];
   if (tmp) (void)hipFree(tmp);
+  *made = st == CMG_OK;
   return st;
 }
 
 // The dense matrix of the smallest levels in precision T, made by the first
 // V-cycle that runs with it (callers of products, transfers or smoothing steps
-// alone do not pay for it).  Synchronous, on the problem's own stream.
+// alone do not pay for it).  Synchronous, on the problem's own stream.  Where its
+// memory cannot be had, every level is run from then on.
 template <typename T>
-cmg_status ensure_dense(cmg_problem* P) {
-  if (P->ghost_local || P->dense_level == 0 || dense_op<T>(P)) return CMG_OK;
+cmg_status ensure_dense(cmg_problem* P, hipStream_t user, size_t scratch = kDenseScratch) {
+  constexpr bool f32 = std::is_same<T, float>::value;
+  bool& tried = f32 ? P->dense32_tried : P->dense64_tried;
+  if (tried || P->ghost_local || P->dense_level == 0) return CMG_OK;
   std::lock_guard<std::recursive_mutex> lock(cmg::device_mutex());
-  if (std::is_same<T, float>::value) TRY(ensure_dense<double>(P));
+  if (f32) TRY(ensure_dense<double>(P, user, scratch));
   RelaxedCapture relaxed;
   if (!P->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking));
   const int64_t n = P->H.levels[P->dense_level].n_dofs;
   void* m = nullptr;
-  if (hipMalloc(&m, static_cast<size_t>(n * n) * sizeof(T)) != hipSuccess)
-    return fail(CMG_ENOMEM, "device allocation failed");
-  P->owned.push_back(m);
-  if constexpr (std::is_same<T, float>::value) {
-    HIP_TRY(cmg::launch_round(n * n, P->dense64, static_cast<float*>(m), P->cap_stream));
-    HIP_TRY(hipStreamSynchronize(P->cap_stream));
-    P->dense32 = static_cast<float*>(m);
-  } else {
-    TRY(build_dense(P, static_cast<double*>(m), P->cap_stream));
-    P->dense64 = static_cast<double*>(m);
+  if ((f32 && !P->dense64) || hipMalloc(&m, static_cast<size_t>(n * n) * sizeof(T)) != hipSuccess) {
+    (void)hipGetLastError();
+    tried = true;
+    return CMG_OK;
   }
-  return CMG_OK;
+  bool made = false;
+  cmg_status st = CMG_OK;
+  if constexpr (f32) {
+    auto round = [&]() -> cmg_status {
+      HIP_TRY(cmg::launch_round(n * n, P->dense64, static_cast<float*>(m), P->cap_stream));
+      HIP_TRY(hipStreamSynchronize(P->cap_stream));
+      return CMG_OK;
+    };
+    st = round();
+    made = st == CMG_OK;
+    if (made) P->dense32 = static_cast<float*>(m);
+  } else {
+    st = build_dense(P, static_cast<double*>(m), scratch, user, P->cap_stream, &made);
+    if (made) P->dense64 = static_cast<double*>(m);
+  }
+  if (made) P->owned.push_back(m);
+  else (void)hipFree(m);
+  tried = st == CMG_OK;
+  return st;
 }
 
 template <typename T>
@@ -1280,12 +1324,12 @@ cmg_status op_vcycle(cmg_problem* p, const double* r, double* z, hipStream_t s) 
 }
 
 // The dense matrix of the current precision, needed by every V-cycle.
-cmg_status ensure_dense_current(cmg_problem* p) {
-  return p->fp32 ? ensure_dense<float>(p) : ensure_dense<double>(p);
+cmg_status ensure_dense_current(cmg_problem* p, hipStream_t s) {
+  return p->fp32 ? ensure_dense<float>(p, s) : ensure_dense<double>(p, s);
 }
 
 cmg_status vcycle_current(cmg_problem* p, const double* r, double* z, hipStream_t s) {
-  TRY(ensure_dense_current(p));
+  TRY(ensure_dense_current(p, s));
   return p->fp32 ? op_vcycle<float>(p, r, z, s) : op_vcycle<double>(p, r, z, s);
 }
 
@@ -1312,13 +1356,13 @@ cmg_status op_apply_multi(cmg_problem* p, int ncol, const double* x, double* y, 
   return gather<double>(p, L, v.r, y, s, ncol);
 }
 
-cmg_status prepare_multi(cmg_problem* p) {
+cmg_status prepare_multi(cmg_problem* p, hipStream_t s) {
   TRY(ensure_multi<double>(p));
   if (p->fp32) {
     TRY(ensure_multi<float>(p));
     TRY(ensure_tiles(p));
   }
-  return ensure_dense_current(p);
+  return ensure_dense_current(p, s);
 }
 
 
@@ -1382,6 +1426,15 @@ size_t hierarchy_bytes(const cmg::Hierarchy& H, int flags) {
 }
 
 }  // namespace
+
+size_t cmg::dense_scratch_bytes(const cmg_problem* p) {
+  auto* P = const_cast<cmg_problem*>(p);  // (the vectors are not touched without a base address)
+  if (P->dense_level == 0) return 0;
+  const int64_t C = dense_batch(P, kDenseScratch);
+  return C > 0 ? dense_vectors(P->lv, P->dense_level, static_cast<size_t>(C), nullptr) : 0;
+}
+
+int cmg::make_dense(cmg_problem* p, size_t scratch) { return ensure_dense<double>(p, nullptr, scratch); }
 
 // Grouped V-cycles: the same V-cycle step of every member as one launch.
 struct cmg_group {
@@ -2110,7 +2163,7 @@ cmg_status cmg_vcycle_multi(cmg_problem* p, int nrhs, const double* r, double* z
   TRY(check_device(p));
   if (!r || !z || nrhs < 1 || nrhs > cmg::kMaxCols) return fail(CMG_EINVAL, "bad multi-column V-cycle arguments");
   if (p->ghost_local) return fail(CMG_EINVAL, "multi-column calls run with the exact ghost coupling only");
-  TRY(prepare_multi(p));
+  TRY(prepare_multi(p, static_cast<hipStream_t>(stream)));
   return vcycle_multi_current(p, nrhs, r, z, static_cast<hipStream_t>(stream));
 }
 
@@ -2120,7 +2173,7 @@ cmg_status cmg_solve_multi(cmg_problem* p, int nrhs, const double* b, double* x,
   if (!b || !x || !(rtol > 0.0) || maxit < 1 || nrhs < 1 || nrhs > cmg::kMaxCols)
     return fail(CMG_EINVAL, "bad multi-column solve arguments");
   if (p->ghost_local) return fail(CMG_EINVAL, "multi-column calls run with the exact ghost coupling only");
-  TRY(prepare_multi(p));
+  TRY(prepare_multi(p, static_cast<hipStream_t>(stream)));
   auto s = static_cast<hipStream_t>(stream);
   const int L = p->H.cfg.n_levels - 1;
   const int64_t n = p->H.levels[L].n_dofs;
@@ -2212,7 +2265,7 @@ cmg_status cmg_group_create(cmg_problem* const* members, int n, cmg_group** out)
   }
   for (int i = 0; i < n; ++i) {
     if (members[i]->ghost_local) return fail(CMG_EINVAL, "group members run with the exact ghost coupling only");
-    TRY(prepare_multi(members[i]));
+    TRY(prepare_multi(members[i], nullptr));
   }
   auto* g = new cmg_group();
   g->m.assign(members, members + n);

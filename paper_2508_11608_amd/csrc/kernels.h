@@ -8,6 +8,8 @@
 
 #include <cstdint>
 
+struct cmg_problem;
+
 namespace cmg {
 
 // One level as seen by the kernels (all pointers are device pointers).
@@ -221,6 +223,13 @@ namespace cmg {
 // synchronisation of the library and by the capture of V-cycle graphs, so
 // that the two never overlap across threads (api.cpp).
 std::recursive_mutex& device_mutex();
+
+// Scratch of the first FP64 V-cycle of an uploaded problem (its work vectors while
+// the dense matrix of the smallest levels is made), and that step by itself in
+// at most `scratch` bytes, for a caller that accounts device memory (api.cpp).
+// make_dense returns a cmg_status.
+size_t dense_scratch_bytes(const ::cmg_problem* p);
+int make_dense(::cmg_problem* p, size_t scratch);
 
 // Load vector of f = sum_q amp_q cos(pi kappa_q . x + phase_q) with g = 0 on
 // the finest level, assembled on the device from the quadrature plan of the

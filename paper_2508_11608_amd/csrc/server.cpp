@@ -24,6 +24,7 @@
 // a result is the same alone and in any batch, group or mix.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstdio>
 #include <condition_variable>
@@ -271,6 +272,21 @@ cmg_status acquire(cmg_server* S, const OwnedRequest& rq, Entry** out, cmg_resul
   if (st == CMG_OK) {
     std::lock_guard<std::recursive_mutex> lock(cmg::device_mutex());
     if (hipMalloc(&e.db, vb) != hipSuccess || hipMalloc(&e.dx, vb) != hipSuccess) st = CMG_ENOMEM;
+  }
+  if (st == CMG_OK) {
+    // the dense matrix of the smallest levels is in the footprint; its scratch is
+    // not, and takes what the budget has left (fewer columns at a time, same bits)
+    const size_t want = cmg::dense_scratch_bytes(p);
+    size_t give = 0;
+    {
+      std::lock_guard<std::mutex> lk(S->mu);
+      give = S->used < S->budget ? std::min(want, S->budget - S->used) : 0;
+      S->used += give;
+    }
+    st = static_cast<cmg_status>(cmg::make_dense(p, give));
+    std::lock_guard<std::mutex> lk(S->mu);
+    S->used -= give;
+    S->cv.notify_all();
   }
   res.t_admitted = S->now();
   if (st != CMG_OK) {
