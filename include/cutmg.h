@@ -320,7 +320,9 @@ void cmg_group_destroy(cmg_group* g);
  * launch of a kind whose bit is set is bracketed by HIP events on its stream.
  * Kinds: 0 operator apply / residual, 1 interior colour step, 2 cut colour
  * step (residual + dense solve), 3 cut colour update, 4 prolongation,
- * 5 restriction, 6 coarse solve, 7 layout (zero / scatter / gather),
+ * 5 restriction, 6 coarse solve (always level 0; in a V-cycle whose smallest
+ * levels are one dense matrix, the product with it, and those levels have no
+ * other launches), 7 layout (zero / scatter / gather),
  * 8 CG vector operations (bits 0..15).  Bits 16..23, when non-zero, hold
  * 1 + the one level whose launches are timed (CMG_EINVAL beyond the
  * finest); zero times every level.  cmg_timing synchronises the device,

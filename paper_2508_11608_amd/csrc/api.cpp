@@ -835,11 +835,11 @@ cmg_status smooth(cmg_problem* P, int l, bool post, hipStream_t s, int ncol = 1,
 }
 
 // x_l = M b_l with the exact coarse inverse (l = 0) or the dense V-cycle of the
-// levels 0..l.
+// levels 0..l, timed as the coarse solve of level 0 in both cases.
 template <typename T>
 cmg_status coarse(cmg_problem* P, hipStream_t s, int ncol = 1, bool multi = false, int l = 0) {
   DevLevel& D = P->lv[l];
-  KTimer t(P, kCoarse, l, s);
+  KTimer t(P, kCoarse, 0, s);
   HIP_TRY(cmg::launch_coarse<T>(l > 0 ? dense_op<T>(P) : coarse_inv<T>(P), D.kl64.dof_node,
                                 static_cast<int>(P->H.levels[l].n_dofs), work<T>(D, multi).b, work<T>(D, multi).x,
                                 D.kl64.n_nodes, s, ncol));
