@@ -364,12 +364,8 @@ cmg_status upload_all(cmg_problem* P) {
     k.nn = h.nn;
     k.n_dofs = h.n_dofs;
     k.n_nodes = h.n_nodes;
-    uint8_t *flags, *ghost;
-    int32_t *cut_id, *dn;
+    int32_t* dn;
     double *cm, *tab;
-    TRY(upload(own, h.cell_flags, &flags));
-    TRY(upload(own, h.cut_id, &cut_id));
-    TRY(upload(own, h.ghost_mask, &ghost));
     TRY(upload(own, h.cut_mats, &cm));
     double* cpk;
     const size_t nl = static_cast<size_t>(std::pow(cfg.k + 1, cfg.dim));
@@ -380,26 +376,18 @@ cmg_status upload_all(cmg_problem* P) {
     if (static_cast<int>(packed.size()) != cmg::tables_size(cfg.dim, cfg.k))
       return fail(CMG_EINVAL, "internal: table layout mismatch");
     TRY(upload(own, packed, &tab));
-    k.flags = flags;
-    k.cut_id = cut_id;
-    k.ghost = ghost;
     k.cut_mats = cm;
     k.cut_packed = cpk;
     k.dof_node = dn;
     k.tables = tab;
     k.tables32 = nullptr;
-    int32_t *flow, *cgid, *cfaces, *tiles;
+    int32_t *flow, *tiles;
     uint8_t* fdir;
     TRY(upload(own, h.face_lower, &flow));
     TRY(upload(own, h.face_dir, &fdir));
-    TRY(upload(own, h.cell_gid, &cgid));
-    TRY(upload(own, h.cell_faces, &cfaces));
     k.n_faces = static_cast<int64_t>(h.face_lower.size());
     k.face_lower = flow;
     k.face_dir = fdir;
-    k.cell_gid = cgid;
-    k.cell_faces = cfaces;
-    k.n_cut = h.n_cut;
     {
       std::vector<int32_t> spec, info, sid;
       special_cells(h, cfg.dim, &spec, &info, &sid);
@@ -1381,9 +1369,7 @@ size_t hierarchy_bytes(const cmg::Hierarchy& H, int flags) {
     size_t maxn = 0;
     // cut-cell matrix entries: full (rows of the cut steps) and packed upper triangles (operator)
     const size_t ncm = static_cast<size_t>(h.n_cut) * (nl * nl + nl * (nl + 1) / 2);
-    b64 += h.cell_flags.size() + h.ghost_mask.size() + 4 * (h.cut_id.size() + h.dof_node.size()) +
-           8 * (ncm + nt) + 4 * (h.face_lower.size() + h.cell_gid.size() + h.cell_faces.size() +
-           h.tiles.size()) + h.face_dir.size();
+    b64 += 4 * (h.dof_node.size() + h.face_lower.size() + h.tiles.size()) + h.face_dir.size() + 8 * (ncm + nt);
     b64 += 8 * (3 * static_cast<size_t>(h.n_nodes) + h.face_lower.size() * nw_face);
     b32 += 4 * (ncm + nt + 3 * static_cast<size_t>(h.n_nodes) + h.face_lower.size() * nw_face);
     for (int c = 0; c < 8; ++c) {

@@ -18,20 +18,14 @@ struct KLevel {
   int nn;                    // lattice nodes per direction, k N + 1
   int64_t n_dofs;
   int64_t n_nodes;           // lattice nodes, nn^d (the column stride of lattice vectors)
-  const uint8_t* flags;      // per cell: bit 0 active, bit 1 cut
-  const int32_t* cut_id;     // per cell: index of its cut-cell matrix or -1
-  const uint8_t* ghost;      // per cell: bit 2*dir+side marks a ghost face
   const void* cut_mats;      // n_cut x (k+1)^d x (k+1)^d, scalar type of the path (symmetric)
   const void* cut_packed;    // the same matrices as upper triangles, row-major, (k+1)^d ((k+1)^d + 1) / 2 each
-  int64_t n_cut;             // cut cells
   const int32_t* dof_node;   // lattice node of each DoF, ascending
   const double* tables;      // constant tables (uncut stiffness, 1-D factors, FD, prolongation)
   const float* tables32;     // FP32 path: the tables rounded to FP32 (else null)
   int64_t n_faces;           // ghost faces
   const int32_t* face_lower; // lower cell of every ghost face
   const uint8_t* face_dir;   // its normal direction
-  const int32_t* cell_gid;   // per cell: row of cell_faces or -1
-  const int32_t* cell_faces; // 2d face ids per cell with ghost faces (-1: none)
   int n_tiles;               // operator tiles owning active nodes whose staged cells (-1 .. B-1 around
   const int32_t* tiles;      // the tile) include a special or inactive cell: dense rows and pre-pass values
   int n_tiles_sf;            // the other tiles owning active nodes: every staged cell active and regular,

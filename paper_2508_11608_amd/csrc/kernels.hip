@@ -107,11 +107,6 @@ __device__ __forceinline__ int64_t cell_lin(int D, int N, const int* c) {
   return D == 2 ? c[0] + (int64_t)N * c[1] : c[0] + (int64_t)N * (c[1] + (int64_t)N * c[2]);
 }
 
-template <int D, int K>
-__device__ void load_tables(const double* __restrict__ g, double* s, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) s[i] = g[i];
-}
-
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
