@@ -1824,7 +1824,9 @@ cmg_status cmg_rhs_fourier_device(cmg_problem* p, int n_modes, const int* kappa,
   for (int q = 0; q < n_modes; ++q) {
     for (int j = 0; j < d; ++j) M.kappa[q][j] = kappa[q * d + j];
     M.amp[q] = amp[q];
-    M.phase[q] = phase[q] / M_PI;
+    // phase / pi modulo 2, rounded to a double once reduced
+    const long double t = static_cast<long double>(phase[q]) / 3.14159265358979323846264338327950288L;
+    M.phase[q] = static_cast<double>(t - 2.0L * std::floor(t / 2.0L));
   }
   for (int j = 0; j < d; ++j) {
     for (int q = 0; q < n_modes; ++q) M.ord[j][q] = static_cast<uint8_t>(q);

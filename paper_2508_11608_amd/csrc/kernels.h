@@ -235,7 +235,7 @@ constexpr int kRhsPow = 8;      // complex products before a power is formed ane
 struct RhsModes {
   int n;
   int kappa[kMaxModes][3];
-  double amp[kMaxModes], phase[kMaxModes];  // phase / pi
+  double amp[kMaxModes], phase[kMaxModes];  // phase / pi modulo 2
   uint8_t ord[3][kMaxModes];                // the modes in increasing order of kappa[.][e], per direction e
 };
 struct RhsPlanDev {
