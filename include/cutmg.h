@@ -132,9 +132,12 @@ cmg_status cmg_device_bytes(const cmg_problem* p, int flags, size_t* bytes);
 cmg_status cmg_set_precision(cmg_problem* p, int fp32);
 
 /* Launch shapes chosen by launch size: cut colour steps of fewer than
- * small_cut_launch patches run with more threads per patch block
- * (default 1536; 0 never, a large value always), and the grid-stride operator
- * and interior-patch kernels launch at most max_blocks blocks per column
+ * small_cut_launch patches run with more threads per patch block (default
+ * 1536; 0 never, a large value always).  One column of 3-D Q3 turns to them at a
+ * quarter of that number of patches, several columns in 3-D at a third of it
+ * (patches times groups of 8 columns); Q1, several columns in 2-D and grouped
+ * steps have one shape only.  The grid-stride operator and interior-patch
+ * kernels launch at most max_blocks blocks per column
  * (default 2048, >= 1).  The arithmetic of every node is the same in every
  * configuration, so results are bitwise independent of these choices; tests
  * use it to run the configurations of large levels on small ones.  Host only. */

@@ -241,7 +241,7 @@ float* dense_op<float>(cmg_problem* P) { return P->dense32; }
 // bytes (33 MB at the limit, about 10 us) in place of the chain of its levels:
 // V-cycle 382 -> 159 us (disc, Q2, 32^2: levels 1 and 2), 1341 -> 939 us (circle,
 // Q2, 512^2: 1 to 3), 1228 -> 902 us (ball, Q2, 32^3: 1).  Making it costs the
-// first V-cycle n columns of the one it replaces, 1 ms (n = 529) to 9 ms (n =
+// first V-cycle n columns of the one it replaces, 0.6 ms (n = 529) to 6.5 ms (n =
 // 1,701), which one to three solves give back; at n = 4,096 it would be tens of
 // ms.  It takes work vectors of a batch of columns on the whole lattices, at most
 // kDenseScratch bytes for as long as that lasts; a level whose lattices do not

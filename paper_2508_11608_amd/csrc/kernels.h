@@ -89,7 +89,8 @@ constexpr int kMaxCols = 8;  // columns (right-hand sides) of one multi-column l
 // a small one.  Results do not depend on them beyond rounding-free choices:
 // the arithmetic of every node is the same for any block size and grid cap.
 struct LaunchPolicy {
-  int small_cut_launch = 1536;  // cut colour steps with fewer patches use more threads per patch block
+  int small_cut_launch = 1536;  // cut colour steps with fewer patches (one column of 3-D Q3: a quarter of it,
+                                // several columns in 3-D: a third) use more threads per patch block
   unsigned max_blocks = 2048;   // grid cap of the grid-stride kernels (operator tiles, interior patches)
 };
 

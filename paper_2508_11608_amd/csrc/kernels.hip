@@ -56,8 +56,10 @@ struct Shape {
   static constexpr int NC1 = 2 * K + 1;            // patch closure nodes per direction
   static constexpr int NC = Pow<NC1, D>::v;
   // patches per 256-thread block of the interior step; Q1 (one node a patch)
-  // stays at 64: 256 took 111 KB of LDS, one block a CU and 13 blocks a launch
-  // (off-centre ball, 64^3 cells: step 10.3 -> 7.1 us)
+  // stays at 64: 256 make few blocks (in 3-D 13 at 64^3 cells, with 111 KB of LDS
+  // each).  Off-centre ball, 64^3 cells: step 10.3 -> 7.1 us; off-centre disc, with
+  // 256, 128, 64, 32, 16 patches a block: 1024^2 cells 8.2, 7.7, 7.8, 8.7, 11.3 us
+  // (V-cycle 611, 595, 586, 594, 616 us), 256^2 cells 7.1, 6.5, 6.5, 6.6, 6.5 us
   static constexpr int PPB = NP == 1 ? 64 : 256 / NP;
   // table layout (doubles), see LevelTables on the host
   static constexpr int T_KCELL = 0;
@@ -1756,8 +1758,12 @@ __global__ __launch_bounds__(TH) void k_cut_solve(KLevel L, CutGroupDev G, const
 // cell row with 8 accumulators, a separate update) was bound by one patch's
 // serial chain and by LDS reads (one 8-column row of x per matrix entry).
 // Union of 8 spheres, Q3, 64^3 cells, 8 columns, FP32: finest step with jumps
-// and update 317 -> 150 us, V-cycle 23.0 -> 10.5 ms; bound by one patch's chain
-// of loads, LDS exchanges and dependent products at 4 blocks per CU (LDS).
+// and update 317 -> 144 us, V-cycle 23.0 -> 9.3 ms.  That step is bound by what it
+// moves: 508 MB (287 MB with every closure, cell and inverse read once) at 3.5
+// TB/s, three quarters of a copy's rate, with 4 blocks a CU (LDS) to keep loads in
+// flight; texture units 55%, LDS 19%, matrix cores 11% busy.  FP64: 896 MB (570) in
+// 256 us, also 3.5 TB/s, at 2 blocks a CU.  A small launch is bound by one patch's
+// chain of loads, LDS exchanges and dependent products.
 template <int D, int K, typename T, int NW_>
 struct ColsShape {
   using S = Shape<D, K>;
