@@ -942,16 +942,18 @@ int64_t dense_batch(cmg_problem* P, size_t scratch) {
 // The matrix M = dense64 of the V-cycle of the levels 0..dense_level: their FP64
 // V-cycle applied to the unit vectors on stream s, a batch of columns per launch
 // sequence (a column does not depend on the others), on work vectors that are
-// released again.  Without room for those, a column at a time on the problem's
-// own vectors, which no other call may be using then: *made stays false where
-// that cannot be waited for (the caller's stream is being captured).
+// released again.  Without room for as many, on the problem's own vectors (its
+// multi-column ones where they are there, else a column at a time), which no
+// other call may be using then: *made stays false where that cannot be waited
+// for (the caller's stream is being captured).
 cmg_status build_dense(cmg_problem* P, double* M, size_t scratch, hipStream_t user, hipStream_t s, bool* made) {
   const int l0 = P->dense_level;
   const int64_t n = P->H.levels[l0].n_dofs;
+  const int64_t own_cols = std::min<int64_t>(n, P->m64_ready ? cmg::kMaxCols : 1);
   int64_t batch = dense_batch(P, scratch);
   void* tmp = nullptr;
   const size_t bytes = batch > 0 ? dense_vectors(P->lv, l0, static_cast<size_t>(batch), nullptr) : 0;
-  if (batch > 0 && hipMalloc(&tmp, bytes) != hipSuccess) {
+  if (batch >= own_cols && hipMalloc(&tmp, bytes) != hipSuccess) {
     (void)hipGetLastError();
     tmp = nullptr;
   }
@@ -959,12 +961,12 @@ cmg_status build_dense(cmg_problem* P, double* M, size_t scratch, hipStream_t us
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (user && hipStreamIsCapturing(user, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return CMG_OK;
     HIP_TRY(hipDeviceSynchronize());
-    batch = 1;
+    batch = own_cols;
   }
   std::vector<Vecs<double>> own(l0 + 1);
   for (int l = 0; l <= l0; ++l) {
     own[l] = P->lv[l].m64;
-    if (!tmp) P->lv[l].m64 = P->lv[l].v64;
+    if (!tmp && !P->m64_ready) P->lv[l].m64 = P->lv[l].v64;
   }
   if (tmp) (void)dense_vectors(P->lv, l0, static_cast<size_t>(batch), static_cast<double*>(tmp));
   const unsigned timed = P->timing_mask;
@@ -1420,7 +1422,10 @@ size_t cmg::dense_scratch_bytes(const cmg_problem* p) {
   return C > 0 ? dense_vectors(P->lv, P->dense_level, static_cast<size_t>(C), nullptr) : 0;
 }
 
-int cmg::make_dense(cmg_problem* p, size_t scratch) { return ensure_dense<double>(p, nullptr, scratch); }
+int cmg::make_dense(cmg_problem* p, size_t scratch) {
+  TRY(ensure_multi<double>(p));  // every solve of the caller needs them, and they do without scratch
+  return ensure_dense<double>(p, nullptr, scratch);
+}
 
 // Grouped V-cycles: the same V-cycle step of every member as one launch.
 struct cmg_group {

@@ -221,8 +221,9 @@ std::recursive_mutex& device_mutex();
 
 // Scratch of the first FP64 V-cycle of an uploaded problem (its work vectors while
 // the dense matrix of the smallest levels is made), and that step by itself in
-// at most `scratch` bytes, for a caller that accounts device memory (api.cpp).
-// make_dense returns a cmg_status.
+// at most `scratch` bytes, for a caller that accounts device memory and solves
+// with the multi-column vectors, which are made here too (api.cpp).  make_dense
+// returns a cmg_status.
 size_t dense_scratch_bytes(const ::cmg_problem* p);
 int make_dense(::cmg_problem* p, size_t scratch);
 
